@@ -62,9 +62,10 @@ typedef enum {
 typedef enum {
     /* everything in FP64 */
     FMM_FP64 = 0,
-    /* P2P, P2M, L2P and the expansions of levels >= 4 (their M2M, M2L and
-     * L2L) in FP32 with cell-local coordinates; the P2P potential and the
-     * leaf multipoles summed in FP64; levels 0-3, the lattice operator, the
+    /* P2P, P2M, L2P and the multipoles and M2L operators of levels >= 4 in
+     * FP32 with cell-local coordinates; the P2P potential and the leaf
+     * multipoles summed in FP64; levels 0-3, the M2L's sums and the locals of
+     * every level that takes it as a convolution, the lattice operator, the
      * charged-system, quadrupole and dipole terms and the energy reduction
      * in FP64 */
     FMM_MIXED = 1,
@@ -76,10 +77,11 @@ typedef enum {
      * the RMS relative potential error is about 1.4e-2 and the force error
      * about 4e-4 at every order p */
     FMM_MIXED_BF16_M2L = 2,
-    /* as FMM_MIXED, but the FP32 levels' M2L writes every operator and
+    /* as FMM_MIXED on the levels whose M2L is a convolution (fmm_plan_info
+     * [11]); the FP32 levels beyond them write every M2L operator and
      * multipole entry as the sum of two FP16 numbers (hi + lo, with exact
      * power-of-two row and column scales keeping them in FP16's range) and
-     * forms hi*hi + hi*lo + lo*hi on the FP16 matrix cores with FP32
+     * form hi*hi + hi*lo + lo*hi on the FP16 matrix cores with FP32
      * accumulation, partial sums flushed to FP64 after every list entry: about
      * 2^-22 relative per product against 2^-24 for FP32 operands.  Orders
      * 11 and 12 run the folded orbit list (all four row classes in one
@@ -96,8 +98,13 @@ typedef enum {
  * interaction list at every level is the children of the parent's +-2
  * neighbours minus the own +-2 block (875 cells, 1206 distinct offsets).
  * Defaults: FMM_FP64, kappa = 3/box, null stream.
- * Precomputes in FP64 on the host the scale-invariant M2M / M2L / L2L
- * operators and the lattice tensor of eq. 12, and uploads them.
+ * Precomputes in FP64 the scale-invariant M2M / M2L / L2L operators and the
+ * lattice tensor of eq. 12.  The M2L of levels 1 .. 6 runs as a convolution
+ * over the level's periodic grid with operators per wave number on the device:
+ * about 0.42 8^levels K^2 elements of the level's type (27 Kp^2 per triple of
+ * wave numbers; 1,000,000 atoms, levels 5, p 12: 1.4 GB in FP32, 2.7 GB in
+ * FP64).  A level whose operators would take more than 64 GiB or a quarter of
+ * the device's memory, or find no memory, takes the interaction lists.
  * On success *out owns them until fmm_destroy.  On failure *out is NULL.
  */
 fmm_status fmm_plan(double box, int levels, int p, fmm_plan_t *out);
@@ -432,8 +439,12 @@ fmm_status fmm_profile_read(fmm_plan_t plan, double *ms, int64_t *calls);
  *   [10] operator rows the matrix cores run per list entry (folded: each row
  *       class padded to whole 16-row blocks; plain: Kp, and for the plain
  *       split-FP16 kernel 64 ceil(n / 4) per row group of n blocks; >= K)
+ *   [11] levels 1 .. [11] whose M2L runs as a convolution over the periodic
+ *       grid instead ([5]-[7] and [10] describe the interaction lists that the
+ *       finer levels, FMM_MIXED_BF16_M2L and FMM_UV_SPARSE take); 0 for a
+ *       batch plan
  */
-#define FMM_INFO_COUNT 11
+#define FMM_INFO_COUNT 12
 fmm_status fmm_plan_info(fmm_plan_t plan, int64_t *info, int n);
 
 /* Message of the last failed call on this plan (never NULL; "" if none).

@@ -181,7 +181,7 @@ def fmm_plan_options(plan: Plan, boundary: int = FMM_BOUNDARY_CONDUCTING, uv_sch
 
 
 INFO_KEYS = ("levels", "p", "K", "Kp", "precision", "m2l_scheme", "m2l_entries", "m2l_launches", "fp64_levels",
-             "p2p_groups", "m2l_rows")
+             "p2p_groups", "m2l_rows", "m2l_conv_levels")
 
 
 def fmm_plan_info(plan: Plan) -> dict:

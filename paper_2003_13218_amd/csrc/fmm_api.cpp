@@ -59,12 +59,21 @@ struct OpSet {
     // over the offsets that reach the same source cell (alias_ops), their
     // lists (8 x n^3 ids) and offsets (the residues of t modulo n)
     DeviceBuf alias_ops[2], alias_il[2], alias_off[2];
+    // convolution form of the M2L: coefficient table, operators of the
+    // reflection representatives and their index, and per level its columns'
+    // table, cosines and blocks ([0] FP32, [1] FP64); conv_no: no memory for them
+    DeviceBuf conv_tab, conv_reps, conv_index, conv_pair[kConvMaxLevel + 1], conv_trig[kConvMaxLevel + 1];
+    DeviceBuf conv_ops[kConvMaxLevel + 1][2];
+    bool conv_no[kConvMaxLevel + 1][2] = {};
     ~OpSet() {
         DeviceBuf *b[] = {&ops32, &ops64, &opsbf, &ops16, &scale16, &il, &offv, &pairs, &rowmap, &rowpos, &zeros,
                           &tree32, &tree64,
                           &alias_ops[0], &alias_ops[1],
                           &alias_il[0], &alias_il[1], &alias_off[0], &alias_off[1]};
         for (DeviceBuf *x : b) x->release();
+        for (DeviceBuf *x : {&conv_tab, &conv_reps, &conv_index}) x->release();
+        for (int l = 0; l <= kConvMaxLevel; ++l)
+            for (DeviceBuf *x : {&conv_pair[l], &conv_trig[l], &conv_ops[l][0], &conv_ops[l][1]}) x->release();
     }
 };
 
@@ -94,6 +103,7 @@ struct fmm_plan {
     // constant, applied exactly in FP64 as phi += t00 Q / b instead of through
     // the level-0 operator, so it never passes through FP32 arrays
     double t00 = 0.0;
+    size_t conv_budget = 0;  // largest block set of a convolution level (see conv_levels)
     int top_fp64 = 3;  // mixed mode: tree levels 1..3 in FP64 (see top_fp64_levels)
     double q_tree = 0.0;  // level-0 monopole of the last fmm_energy_forces tree
     double last_energy = 0.0;  // energy of the last fmm_energy_forces call
@@ -357,27 +367,115 @@ static int upper_m2l_levels(fmm_plan_t pl) {
     return std::max(0, std::min(top_fp64_levels(pl), pl->levels - 2));
 }
 
+// Levels 1 .. conv_levels(pl) take the M2L as a convolution (k_conv.hip), the
+// finer ones the interaction lists.  The convolution does a level in about the
+// time its blocks take to stream (finest level of the 1M-atom box, p = 12: lists
+// 5.9 ms, convolution 0.7 ms in FP32; 13.4 and 1.1 ms in FP64), so it is taken
+// wherever the blocks (their bytes grow with 8^level K^2) fit: levels up
+// to 6 (lines of 64 cells in registers), at most a quarter of the device's
+// memory and 64 GiB for a level (p = 20 at level 6 in FP64: 112 GB).  Levels
+// 1 .. 4 go together or not at all.  The BF16 mode keeps the lists: its
+// operands are that mode's point.
+static int conv_levels(fmm_plan_t pl) {
+    if (pl->prec == FMM_MIXED_BF16_M2L) return 0;
+    const int top = top_fp64_levels(pl);
+    int c = 0;
+    for (int l = 1; l <= std::min(pl->levels, kConvMaxLevel); ++l) {
+        const bool d = l <= top;
+        if (pl->op->conv_no[l][d] || conv_op_bytes(l, pl->p, d ? 8 : 4) > pl->conv_budget) break;
+        c = l;
+    }
+    return c >= std::min(4, pl->levels) ? c : 0;
+}
+
 // The M2L operator sets the plan's current mode needs; want64: the FP64
 // operators whatever the precision (sparse solute pass).
 struct OpNeeds {
+    int conv;
     bool alias, f64, f32, bf, f16;
 };
 static OpNeeds m2l_needs(fmm_plan_t pl, bool want64) {
+    const int top = top_fp64_levels(pl);
     OpNeeds n;
-    n.alias = top_fp64_levels(pl) > 0 || want64;
-    n.f64 = n.alias || want64;
-    n.f32 = pl->prec == FMM_MIXED;
+    n.conv = conv_levels(pl);
+    const bool fine = pl->levels > std::max(n.conv, top);  // list levels in the mode's own operands
+    n.alias = want64 || (n.conv == 0 && top > 0);
+    n.f64 = want64 || top > n.conv;
+    n.f32 = pl->prec == FMM_MIXED && fine;
     n.bf = pl->prec == FMM_MIXED_BF16_M2L;
-    n.f16 = pl->prec == FMM_MIXED_SPLIT16_M2L;
+    n.f16 = pl->prec == FMM_MIXED_SPLIT16_M2L && fine;
     return n;
+}
+static bool conv_ready(fmm_plan_t pl, int levels) {
+    const int top = top_fp64_levels(pl);
+    for (int l = 1; l <= levels; ++l)
+        if (!pl->op->conv_ops[l][l <= top].ptr) return false;
+    return true;
 }
 static bool m2l_ops_ready(fmm_plan_t pl, bool want64) {
     const OpNeeds n = m2l_needs(pl, want64);
-    return (!n.f64 || pl->op->ops64.ptr) && (!n.alias || pl->op->alias_ops[0].ptr) && (!n.f32 || pl->op->ops32.ptr) &&
-           (!n.bf || pl->op->opsbf.ptr) && (!n.f16 || pl->op->ops16.ptr);
+    return conv_ready(pl, n.conv) && (!n.f64 || pl->op->ops64.ptr) && (!n.alias || pl->op->alias_ops[0].ptr) &&
+           (!n.f32 || pl->op->ops32.ptr) && (!n.bf || pl->op->opsbf.ptr) && (!n.f16 || pl->op->ops16.ptr);
+}
+
+// Builds the blocks of the convolution levels that are missing (on the GPU,
+// from the operators of the reflection representatives) and waits for them.  A
+// level that finds no memory is marked and left to the lists.
+static fmm_status ensure_conv_ops(fmm_plan_t pl) {
+    OpSet &o = *pl->op;
+    const int top = top_fp64_levels(pl);
+    auto upload = [&](DeviceBuf &b, const void *src, size_t bytes) {
+        if (b.ptr) return hipSuccess;
+        if (!b.ensure(bytes)) return hipErrorOutOfMemory;
+        const hipError_t e = hipMemcpy(b.ptr, src, bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) b.release();
+        return e;
+    };
+    for (int l = 1; l <= conv_levels(pl); ++l) {
+        const bool d = l <= top;
+        if (o.conv_ops[l][d].ptr) continue;
+        hipError_t e = hipSuccess;
+        if (!o.conv_index.ptr) {
+            std::vector<ConvCoef> tab;
+            std::vector<double> reps;
+            std::vector<int32_t> index;
+            conv_coef_table(pl->p, tab);
+            conv_reps(pl->p, tab, reps, index);
+            e = upload(o.conv_tab, tab.data(), sizeof(ConvCoef) * tab.size());
+            if (e == hipSuccess) e = upload(o.conv_reps, reps.data(), sizeof(double) * reps.size());
+            if (e == hipSuccess) e = upload(o.conv_index, index.data(), sizeof(int32_t) * index.size());
+        }
+        if (e == hipSuccess) {
+            std::vector<int32_t> pair;
+            std::vector<double> trig;
+            conv_pair_base(l, pair);
+            conv_trig(l, trig);
+            e = upload(o.conv_pair[l], pair.data(), sizeof(int32_t) * pair.size());
+            if (e == hipSuccess) e = upload(o.conv_trig[l], trig.data(), sizeof(double) * trig.size());
+        }
+        if (e == hipSuccess && !o.conv_ops[l][d].ensure(conv_op_bytes(l, pl->p, d ? 8 : 4))) e = hipErrorOutOfMemory;
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            o.conv_no[l][d] = true;
+            continue;
+        }
+        if (e == hipSuccess)
+            e = launch_conv_build(l, pl->p, o.conv_reps.as<double>(), o.conv_index.as<int32_t>(),
+                                  o.conv_trig[l].as<double>(), o.conv_tab.as<ConvCoef>(), o.conv_ops[l][d].ptr,
+                                  d ? 8 : 4, nullptr);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        if (e != hipSuccess) {
+            o.conv_ops[l][d].release();
+            return hip_fail(pl, e, "convolution operators");
+        }
+    }
+    return FMM_OK;
 }
 
 static fmm_status ensure_m2l_ops(fmm_plan_t pl, bool want64 = false) {
+    if (m2l_ops_ready(pl, want64)) return FMM_OK;
+    fmm_status st = ensure_conv_ops(pl);
+    if (st != FMM_OK) return st;
     if (m2l_ops_ready(pl, want64)) return FMM_OK;
     const OpNeeds nd = m2l_needs(pl, want64);
     const bool needalias = nd.alias, need64 = nd.f64, need32 = nd.f32, needbf = nd.bf, need16 = nd.f16;
@@ -490,6 +588,9 @@ static fmm_status plan_create(double box, int levels, int p, const std::shared_p
         return s;
     };
     scratch_setup(pl->device);
+    size_t mem = 0;
+    if (hipDeviceTotalMem(&mem, pl->device) != hipSuccess) mem = 0;
+    pl->conv_budget = std::min(mem / 4, (size_t)64 << 30);
     if (pl->device < 64 && !rec_uploaded[pl->device]) {
         RecTables t;
         build_rec_tables(&t);
@@ -535,7 +636,13 @@ extern "C" fmm_status fmm_plan(double box, int levels, int p, fmm_plan_t *out) {
     if (st != FMM_OK) return st;
     // the operators of the default precision are uploaded with the plan
     // (fmm_plan_config and fmm_plan_tuning add what a new mode needs), so an
-    // evaluation allocates only its per-call workspace
+    // evaluation allocates only its per-call workspace.  Block sets of more
+    // than 1 GiB wait for fmm_plan_config or the first evaluation: a program
+    // that goes on to another precision would never use them, and no plan that
+    // large is within the fixed scratch of fmm_energy_forces_noalloc.
+    size_t blocks = 0;
+    for (int l = 1; l <= conv_levels(*out); ++l) blocks += conv_op_bytes(l, p, 8);
+    if (blocks > ((size_t)1 << 30)) return FMM_OK;
     if ((st = ensure_m2l_ops(*out, false)) != FMM_OK) {
         g_plan_error = (*out)->err;
         fmm_destroy(*out);
@@ -619,7 +726,7 @@ extern "C" fmm_status fmm_plan_info(fmm_plan_t pl, int64_t *info, int n) {
     const int64_t v[FMM_INFO_COUNT] = {pl->is_batch ? 0 : pl->levels, pl->p, pl->K, pl->Kp, pl->prec,
                                        plain ? 0 : m2l_scheme(pl->p), plain ? kILSize : m2l_list_entries(pl->p),
                                        launches, pl->is_batch ? pl->top_fp64 : top_fp64_levels(pl), pl->p2p_g,
-                                       rows};
+                                       rows, pl->is_batch ? 0 : conv_levels(pl)};
     for (int i = 0; i < n && i < FMM_INFO_COUNT; ++i) info[i] = v[i];
     return FMM_OK;
 }
@@ -643,6 +750,10 @@ extern "C" fmm_status fmm_plan_options(fmm_plan_t pl, int boundary, int uv_schem
     } else if (changed) {
         pl->have_state = false;
     }
+    // the sparse pass needs the list operators: uploaded here rather than by
+    // its first call, which builds them (and reports) if this fails
+    fmm_plan_t first = pl->is_batch ? pl->sub[0] : pl;
+    if ((uv_scheme & FMM_UV_SPARSE) && hipSetDevice(pl->device) == hipSuccess) (void)ensure_m2l_ops(first, true);
     return FMM_OK;
 }
 
@@ -797,7 +908,8 @@ static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *ph
     // batch, whose boxes already run as parallel graph branches).  The upper
     // tree's small launches wait behind the near field for CU slots; off the
     // plan stream they no longer hold back the finest levels.
-    const int lup = pl->in_batch ? 0 : upper_m2l_levels(pl);
+    const int cl = conv_levels(pl);  // levels whose M2L is a convolution
+    const int lup = pl->in_batch ? 0 : cl == 0 ? upper_m2l_levels(pl) : L >= 5 ? 4 : 0;
     if (lup > 0 && !pl->side_up) return fail(pl, FMM_ERR_STATE, "plan has no side stream for the upper tree");
     hipStream_t su = lup > 0 ? pl->side_up : s;
     auto m2m = [&](int l, hipStream_t ms) {
@@ -821,7 +933,32 @@ static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *ph
     HIPCHK(pl, launch_lattice(pl->M0.as<double>(), pl->L0.as<double>(), pl->lat.as<double>(), p, Kp, su), "lattice");
     stage_end(pl, FMM_STAGE_LATTICE, su);
     stage_begin(pl, FMM_STAGE_M2L);
+    // The convolution of levels 1 .. 4 (in one set of launches) or of one finer
+    // level.  Its two buffers are the level's own locals and a piece of the
+    // list kernels' scratch, of which the plan then has no other use.
+    auto conv = [&](int l0, int l1, const DeviceBuf &scratch, hipStream_t ls) -> hipError_t {
+        ConvLevel lv[kConvMaxBatch];
+        size_t at = 0;
+        for (int l = l0; l <= l1; ++l) {
+            const bool d = l <= top;
+            lv[l - l0] = ConvLevel{l, d, MT(l), LD(l), pl->op->conv_ops[l][d].ptr, pl->op->conv_pair[l].as<int32_t>(),
+                                   scratch.as<double>() + at, LD(l)};
+            at += (size_t)level_cells(l) * Kp;
+        }
+        if (at * sizeof(double) > scratch.bytes) return hipErrorInvalidValue;
+        return launch_conv(lv, l1 - l0 + 1, p, pl->op->conv_tab.as<ConvCoef>(), ls);
+    };
     for (int l = 1; l <= L; ++l) {
+        if (l <= cl) {
+            const int l1 = l == 1 ? std::min(4, L) : l;
+            if (l1 == L) stage_begin(pl, FMM_STAGE_M2L_LEAF);
+            const hipError_t e = l > 1 ? conv(l, l, pl->mflip, s) : conv(1, l1, lup > 0 ? pl->m2l_part_up : pl->m2l_part, su);
+            if (e == hipErrorInvalidValue) return fail(pl, FMM_ERR_DEVICE, "M2L: scratch capacity rejected");
+            HIPCHK(pl, e, "M2L");
+            if (l1 == L) stage_end(pl, FMM_STAGE_M2L_LEAF);
+            l = l1;
+            continue;
+        }
         if (l == L) stage_begin(pl, FMM_STAGE_M2L_LEAF);
         const bool up = l <= lup;
         hipStream_t ls = up ? su : s;
@@ -858,14 +995,15 @@ static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *ph
         HIPCHK(pl, e, "M2L");
         if (l == L) stage_end(pl, FMM_STAGE_M2L_LEAF);
     }
-    // L2L into level l (from level l - 1; level 1 from the lattice's L0)
+    // L2L into level l (from level l - 1; level 1 from the lattice's L0).  The
+    // locals of the convolution's levels are FP64 in every mode, those of list
+    // levels in the level's type.
+    auto ld = [&](int l) { return l <= std::max(top, cl); };
     auto l2l = [&](int l, hipStream_t ls) -> hipError_t {
-        if (l == 1)
-            return top >= 1 ? launch_l2l_mfma<double, double>(1, pl->L0.as<double>(), LD(1), l2l_ops(true), p, Kp, ls)
-                            : launch_l2l_mfma<double, T>(1, pl->L0.as<double>(), LT(1), l2l_ops(true), p, Kp, ls);
+        const double *up = l == 1 ? pl->L0.as<double>() : LD(l - 1);
         const int64_t np = level_cells(l - 1);  // parents
-        if (l <= top) return launch_l2l_mfma<double, double>(np, LD(l - 1), LD(l), l2l_ops(true), p, Kp, ls);
-        if (l - 1 <= top) return launch_l2l_mfma<double, T>(np, LD(l - 1), LT(l), l2l_ops(true), p, Kp, ls);
+        if (ld(l)) return launch_l2l_mfma<double, double>(np, up, LD(l), l2l_ops(true), p, Kp, ls);
+        if (l == 1 || ld(l - 1)) return launch_l2l_mfma<double, T>(np, up, LT(l), l2l_ops(true), p, Kp, ls);
         return launch_l2l_mfma<T, T>(np, LT(l - 1), LT(l), l2l_ops(TD), p, Kp, ls);
     };
     // The upper tree's own L2L steps (into levels 1 .. lup, whose M2L ran on
@@ -882,7 +1020,8 @@ static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *ph
     for (int l = lup + 1; l <= L; ++l) HIPCHK(pl, l2l(l, s), "L2L");
     stage_end(pl, FMM_STAGE_L2L);
     stage_begin(pl, FMM_STAGE_L2P);
-    HIPCHK(pl, launch_l2p<T>(level_cells(L), xq, pl->start.as<int32_t>(), LT(L), p, Kp, h_leaf, phi, field, s, n),
+    HIPCHK(pl, (ld(L) ? launch_l2p<T, double>(level_cells(L), xq, pl->start.as<int32_t>(), LD(L), p, Kp, h_leaf, phi, field, s, n)
+                      : launch_l2p<T, T>(level_cells(L), xq, pl->start.as<int32_t>(), LT(L), p, Kp, h_leaf, phi, field, s, n)),
            "L2P");
     stage_end(pl, FMM_STAGE_L2P);
     return FMM_OK;
@@ -1083,9 +1222,6 @@ extern "C" fmm_status fmm_energy_forces_noalloc(fmm_plan_t pl, int64_t n, const 
     if (pl->device < 0 || pl->device >= 64 || !g_scratch_ptr[pl->device])
         return hip_fail(pl, pl->device >= 0 && pl->device < 64 ? g_scratch_err[pl->device] : hipErrorInvalidDevice,
                         "fmm_energy_forces_noalloc: device address of the scratch array");
-    if (!m2l_ops_ready(pl, false))
-        return fail(pl, FMM_ERR_STATE, "fmm_energy_forces_noalloc: the operators of the current mode are not on the "
-                                       "device (fmm_plan, fmm_plan_config and fmm_plan_tuning upload them)");
     std::vector<WsItem> items;
     tree_layout(pl, items);
     atom_layout(pl, n, items);
@@ -1097,6 +1233,9 @@ extern "C" fmm_status fmm_energy_forces_noalloc(fmm_plan_t pl, int64_t n, const 
                     "fmm_energy_forces_noalloc: " + std::to_string(n) + " atoms on this plan need " +
                         std::to_string(need) + " bytes of scratch, more than the " +
                         std::to_string(kNoAllocScratchBytes) + " available");
+    if (!m2l_ops_ready(pl, false))
+        return fail(pl, FMM_ERR_STATE, "fmm_energy_forces_noalloc: the operators of the current mode are not on the "
+                                       "device (fmm_plan, fmm_plan_config and fmm_plan_tuning upload them)");
     char *base = static_cast<char *>(g_scratch_ptr[pl->device]);
     ScratchViews views;
     size_t at = 0;

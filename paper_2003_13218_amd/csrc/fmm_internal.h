@@ -113,8 +113,9 @@ hipError_t launch_p2m(int64_t nleaf, const void *xq, const int32_t *start, T *M,
 hipError_t launch_lattice(const double *M0, double *L0, const double *AT, int p, int Kp,
                           hipStream_t s);
 // natoms: atoms of the tree (sets the leaves per workgroup)
-template <typename T>
-hipError_t launch_l2p(int64_t nleaf, const void *xq, const int32_t *start, const T *L, int p,
+// (TL: type of the locals, FP32 only with FP32 atoms)
+template <typename T, typename TL>
+hipError_t launch_l2p(int64_t nleaf, const void *xq, const int32_t *start, const TL *L, int p,
                       int Kp, double h, double *phi, T *field, hipStream_t s, int64_t natoms);
 
 // ---------------------------------------------------------------------------
@@ -311,6 +312,44 @@ hipError_t launch_m2l_split16(int level, const void *ops, const int32_t *list, c
 // any nops row-major K x K operators into the matrix-core lane order
 template <typename T>
 void swizzle_ops(int p, int nops, const double *ops_rowmajor, T *out);
+
+// ---------------------------------------------------------------------------
+// conv_layout.cpp (host) and k_conv.hip (kernels): the M2L of a whole level as
+// a convolution over the periodic grid of its parents (k_conv.hip has the
+// algebra).
+// ---------------------------------------------------------------------------
+constexpr int kConvMaxLevel = 6;  // line transforms of 2 .. 64 cells
+constexpr int kConvTypes = 27;    // K x K blocks stored per wave-number triple
+struct ConvCoef {                 // position in the convolution's coefficient order ->
+    int16_t sto, mir;             // storage index; position of its x <-> y mirror image
+    uint8_t flips;                // bit a: the reflection of axis a flips its sign
+    uint8_t mneg, lneg;           // 1: the mirror flips the sign of a multipole / a local
+    uint8_t pad;
+};
+void conv_coef_table(int p, std::vector<ConvCoef> &out);
+int conv_orbits(int level);  // wave-number triples kx >= ky, kz of a level
+size_t conv_op_bytes(int level, int p, size_t elem);
+void conv_reps(int p, const std::vector<ConvCoef> &tab, std::vector<double> &out, std::vector<int32_t> &index);
+void conv_pair_base(int level, std::vector<int32_t> &base);
+void conv_trig(int level, std::vector<double> &t);
+
+// One level of a convolution launch.  M: the level's multipoles (FP64 when
+// fp64, else FP32); L: its locals (FP64); ops: its blocks in the type of M;
+// pair: conv_pair_base; P, Q: two buffers of 8^level Kp doubles (Q may be L).
+struct ConvLevel {
+    int level, fp64;
+    const void *M;
+    double *L;
+    const void *ops;
+    const int32_t *pair;
+    double *P, *Q;
+};
+constexpr int kConvMaxBatch = 4;  // levels a launch takes together (1 .. 4)
+// builds the blocks of one level (elem 4 or 8) from conv_reps' operators
+hipError_t launch_conv_build(int level, int p, const double *reps, const int32_t *index, const double *trig,
+                             const ConvCoef *tab, void *ops, size_t elem, hipStream_t s);
+// M2L of the given levels (all <= 4, or one level of 5 or 6)
+hipError_t launch_conv(const ConvLevel *lv, int nlv, int p, const ConvCoef *tab, hipStream_t s);
 
 // k_tree.hip: M2M / L2L on the matrix cores; ops = 8 swizzled octant
 // operators in the compute precision (FP64 if either side is FP64)

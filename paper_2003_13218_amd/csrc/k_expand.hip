@@ -475,18 +475,26 @@ template <typename T, int P> constexpr int l2p_min_waves() {
     return (sizeof(T) == 8 && P >= 9 && P <= 12) ? 3 : 1;
 }
 
-template <typename T, int P>
+// byte offset of the constants behind the group's expansions
+template <typename T> __host__ __device__ inline size_t l2p_cst_at(int gl, int per) {
+    return ((size_t)gl * per * sizeof(T) + 7) / 8 * 8;
+}
+
+// The constant L~_0^0 of a leaf, by far its largest term (every image and
+// neighbour charge adds to it), stays in FP64 where the locals are: rounded to
+// FP32 it would shift the potential of all atoms of the leaf together.
+template <typename T, typename TL, int P>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(l2p_min_waves<T, P>()))) void k_l2p(
-    int64_t nleaf, const T *__restrict__ xq,
-                                             const int32_t *__restrict__ start, const T *__restrict__ L, int Kp,
-                                             T inv_h, T inv_h2, double *__restrict__ phi, T *__restrict__ field,
-                                             int gl) {
+    int64_t nleaf, const T *__restrict__ xq, const int32_t *__restrict__ start, const TL *__restrict__ L, int Kp,
+    double inv_hd, T inv_h2, double *__restrict__ phi, T *__restrict__ field, int gl) {
     constexpr int K = (P + 1) * (P + 1);
     constexpr int Kg = P * P;
     constexpr int per = K + 3 * Kg;  // per leaf: L~, then G~x, G~y, G~z
     extern __shared__ unsigned char smem_raw[];
     T *sm = reinterpret_cast<T *>(smem_raw);
-    int32_t *sst = reinterpret_cast<int32_t *>(smem_raw + (size_t)gl * per * sizeof(T));  // the group's leaf starts
+    double *cst = reinterpret_cast<double *>(smem_raw + l2p_cst_at<T>(gl, per));  // the group's constants
+    int32_t *sst = reinterpret_cast<int32_t *>(cst + gl);                         // and leaf starts
+    const T inv_h = (T)inv_hd;
     const int tid = threadIdx.x;
     const int64_t l0 = blockIdx.x * (int64_t)gl;
     const int nl = (int)min((int64_t)gl, nleaf - l0);
@@ -494,7 +502,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(l2p_min_wav
     if (a1 <= a0) return;  // uniform per block
     for (int i = tid; i < nl * K; i += 256) {
         const int li = i / K, j = i - li * K;
-        sm[li * per + j] = L[(l0 + li) * Kp + j];
+        const TL v = L[(l0 + li) * Kp + j];
+        sm[li * per + j] = (T)v;
+        if (j == 0) cst[li] = (double)v;
     }
     if (tid <= nl) sst[tid] = start[l0 + tid];
     __syncthreads();
@@ -533,14 +543,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(l2p_min_wav
         const T *Gx = Ls + K, *Gy = Gx + Kg, *Gz = Gy + Kg;
         const T *a = xq + 4 * (int64_t)s;
         const T x = a[0] * inv_h, y = a[1] * inv_h, z = a[2] * inv_h;
-        double ph = 0;  // potential accumulated in FP64 (see k_p2p)
+        double ph = cst[li];  // potential accumulated in FP64 (see k_p2p)
         T gx = 0, gy = 0, gz = 0;
         // with P a compile-time constant every index below is one too: the
         // expansions are read from LDS at fixed offsets from the leaf's base
         regular_hat_unrolled<T, P>(x, y, z, [&](int n, int m, T re, T im) {
             if (m == 0) {
                 const int k = n * n;
-                ph += (double)(re * Ls[k]);
+                if (n > 0) ph += (double)(re * Ls[k]);
                 if (n < P) { gx += re * Gx[k]; gy += re * Gy[k]; gz += re * Gz[k]; }
             } else {
                 const int k = n * n + 2 * m - 1;
@@ -552,7 +562,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(l2p_min_wav
                 }
             }
         });
-        phi[s] = ph * (double)inv_h;
+        phi[s] = ph * inv_hd;
         field[3 * (int64_t)s + 0] = -gx * inv_h2;
         field[3 * (int64_t)s + 1] = -gy * inv_h2;
         field[3 * (int64_t)s + 2] = -gz * inv_h2;
@@ -561,8 +571,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(l2p_min_wav
 
 // leaves per workgroup: about 256 atoms per group at the mean occupancy,
 // within 48 KB of LDS
-template <typename T, int P>
-static hipError_t launch_l2p_p(int64_t nleaf, const void *xq, const int32_t *start, const T *L, int Kp, double h,
+template <typename T, typename TL, int P>
+static hipError_t launch_l2p_p(int64_t nleaf, const void *xq, const int32_t *start, const TL *L, int Kp, double h,
                                double *phi, T *field, hipStream_t s, int64_t natoms) {
     constexpr int K = (P + 1) * (P + 1);
     const size_t per = (size_t)(K + 3 * P * P) * sizeof(T);
@@ -571,18 +581,18 @@ static hipError_t launch_l2p_p(int64_t nleaf, const void *xq, const int32_t *sta
     gl = std::max(1, std::min(gl, (int)((48 * 1024) / per)));
     gl = std::min(gl, 64);
     const int64_t g = (nleaf + gl - 1) / gl;
-    const size_t lds = (size_t)gl * per + (size_t)(gl + 1) * sizeof(int32_t);
-    hipLaunchKernelGGL((k_l2p<T, P>), dim3((unsigned)g), dim3(256), lds, s, nleaf, (const T *)xq, start, L, Kp,
-                       (T)(1.0 / h), (T)(1.0 / (h * h)), phi, field, gl);
+    const size_t lds = l2p_cst_at<T>(gl, K + 3 * P * P) + (size_t)gl * sizeof(double) + (size_t)(gl + 1) * sizeof(int32_t);
+    hipLaunchKernelGGL((k_l2p<T, TL, P>), dim3((unsigned)g), dim3(256), lds, s, nleaf, (const T *)xq, start, L, Kp,
+                       1.0 / h, (T)(1.0 / (h * h)), phi, field, gl);
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_l2p(int64_t nleaf, const void *xq, const int32_t *start, const T *L, int p, int Kp,
+template <typename T, typename TL>
+hipError_t launch_l2p(int64_t nleaf, const void *xq, const int32_t *start, const TL *L, int p, int Kp,
                       double h, double *phi, T *field, hipStream_t s, int64_t natoms) {
     switch (p) {
 #define FMM_L2P_CASE(P) \
-    case P: return launch_l2p_p<T, P>(nleaf, xq, start, L, Kp, h, phi, field, s, natoms);
+    case P: return launch_l2p_p<T, TL, P>(nleaf, xq, start, L, Kp, h, phi, field, s, natoms);
         FMM_L2P_CASE(0) FMM_L2P_CASE(1) FMM_L2P_CASE(2) FMM_L2P_CASE(3) FMM_L2P_CASE(4) FMM_L2P_CASE(5)
         FMM_L2P_CASE(6) FMM_L2P_CASE(7) FMM_L2P_CASE(8) FMM_L2P_CASE(9) FMM_L2P_CASE(10) FMM_L2P_CASE(11)
         FMM_L2P_CASE(12) FMM_L2P_CASE(13) FMM_L2P_CASE(14) FMM_L2P_CASE(15) FMM_L2P_CASE(16) FMM_L2P_CASE(17)
@@ -591,9 +601,11 @@ hipError_t launch_l2p(int64_t nleaf, const void *xq, const int32_t *start, const
         default: return hipErrorInvalidValue;
     }
 }
-template hipError_t launch_l2p<float>(int64_t, const void *, const int32_t *, const float *, int, int,
-                                      double, double *, float *, hipStream_t, int64_t);
-template hipError_t launch_l2p<double>(int64_t, const void *, const int32_t *, const double *, int, int,
-                                       double, double *, double *, hipStream_t, int64_t);
+template hipError_t launch_l2p<float, float>(int64_t, const void *, const int32_t *, const float *, int, int, double,
+                                             double *, float *, hipStream_t, int64_t);
+template hipError_t launch_l2p<float, double>(int64_t, const void *, const int32_t *, const double *, int, int, double,
+                                              double *, float *, hipStream_t, int64_t);
+template hipError_t launch_l2p<double, double>(int64_t, const void *, const int32_t *, const double *, int, int, double,
+                                               double *, double *, hipStream_t, int64_t);
 
 }  // namespace fmm
