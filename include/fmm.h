@@ -336,10 +336,8 @@ fmm_status fmm_lattice_tensor(fmm_plan_t plan, double *out, int64_t cap);
  * fmm_energy_forces_batch -- energies of all boxes.  Box w holds the atoms
  *   offsets[w] .. offsets[w+1]-1 (host, nbox + 1 non-decreasing int64) of
  *   pos (device, x 3 FP64) and q (device FP64); energies: host out, nbox;
- *   forces: device out (same rows as pos) or NULL.  The boxes run as
- *   parallel branches of one HIP graph launch on the plan stream; the graph
- *   is captured on the first call and replayed while offsets, the three
- *   pointers and the precision stay the same (inputs may change in place).
+ *   forces: device out (same rows as pos) or NULL.  The boxes run side by side
+ *   on streams of their own, forked from and joined into the plan stream.
  *   Empty boxes give 0.  Caches the per-box state for
  *   fmm_solute_solvent_energy_batch and fmm_lambda_energy_batch.
  *
@@ -358,8 +356,8 @@ fmm_status fmm_lattice_tensor(fmm_plan_t plan, double *out, int64_t cap);
  * fmm_batch_set_tuning -- sets every box's depth (levels[w] in [1, 10]) and
  *   P2P source-group count (p2p_groups[w]: 0, 1, 2, 4, 8 or 16), host nbox ints
  *   each; NULL keeps that setting.  Every value is checked before any box
- *   changes (FMM_ERR_INVALID).  Waits for the device; the next batch call
- *   captures its graph anew.
+ *   changes (FMM_ERR_INVALID).  Waits for the device; the next solute-solvent
+ *   batch call captures its graph anew.
  *
  * fmm_autotune_batch_cached -- fmm_autotune_batch with a cache file
  *   (cache_path: a text file, created if absent, one line per tuned batch).

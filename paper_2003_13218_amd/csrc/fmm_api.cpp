@@ -154,8 +154,8 @@ struct fmm_plan {
     int p2p_g = 0;  // P2P source groups; 0 = chosen from the leaf occupancy
     bool in_batch = false;  // sub-plan of a batch plan
 
-    // batch plans (fmm_plan_batch): one sub-plan per box, run as parallel
-    // branches of one captured HIP graph per call signature
+    // batch plans (fmm_plan_batch): one sub-plan per box, run on parallel
+    // streams (the solute-solvent pass as one captured HIP graph)
     bool is_batch = false;
     std::vector<fmm_plan_t> sub;
     std::vector<int64_t> sub_natoms;  // atom counts the levels were chosen for
@@ -166,7 +166,7 @@ struct fmm_plan {
     struct Graph {
         hipGraphExec_t exec = nullptr;
         std::vector<int64_t> key;
-    } g_ef, g_uv;
+    } g_uv;
     std::vector<int64_t> batch_off;  // offsets of the last batch evaluation
     bool batch_state = false;
 };
@@ -225,11 +225,10 @@ static void scratch_setup(int device) {
 }
 
 static void batch_drop_graphs(fmm_plan_t pl) {
-    for (auto *g : {&pl->g_ef, &pl->g_uv}) {
-        if (g->exec) (void)hipGraphExecDestroy(g->exec);
-        g->exec = nullptr;
-        g->key.clear();
-    }
+    fmm_plan::Graph &g = pl->g_uv;
+    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    g.exec = nullptr;
+    g.key.clear();
 }
 
 // Stage events: begin/end recorded on the plan stream when profiling.
@@ -796,7 +795,7 @@ static void tree_layout(fmm_plan_t pl, std::vector<WsItem> &v) {
     v.push_back({&pl->pstart, sizeof(int32_t) * (nleaf + 1), true});
     v.push_back({&pl->scan, sizeof(int32_t) * scan_scratch_len(nleaf), true});
     v.push_back({&pl->scalars, sizeof(double) * kScalars, true});
-    v.push_back({&pl->flag, sizeof(int) * 4, true});
+    v.push_back({&pl->flag, sizeof(int) * kFlags, true});
     v.push_back({&pl->partials, sizeof(double) * 2 * 16 * 1024, true});
     v.push_back({&pl->sflag, sizeof(uint32_t) * (size_t)(1 + cells), false});
 }
@@ -840,22 +839,33 @@ static fmm_status ensure_workspace(fmm_plan_t pl, int64_t n) {
     return FMM_OK;
 }
 
-// a1 + a2: wrap, bin, Morton key, stable sort, leaf ranges.
+static int p2p_groups(int64_t n, int levels) {
+    // 4 groups of 16 target slots fit the 10-40 atom leaves of water boxes at
+    // 4-7 A leaf edges best (measured: 30 atoms/leaf G 4 < 2 < 8; 11 atoms/leaf
+    // G 4 < 8); sparse leaves take more groups, crowded ones fewer
+    const double occ = (double)n / (double)level_cells(levels);
+    if (occ > 48.0) return 2;
+    if (occ > 5.0) return 4;
+    if (occ > 2.5) return 8;
+    return 16;
+}
+static int plan_groups(fmm_plan_t pl, int64_t n) { return pl->p2p_g ? pl->p2p_g : p2p_groups(n, pl->levels); }
+
+// a1 + a2 up to the atoms' segments: wrap, bin, Morton key, leaf ranges, scatter
 static fmm_status sort_atoms(fmm_plan_t pl, int64_t n, const double *pos, const double *q) {
     hipStream_t s = pl->stream;
     const int64_t nleaf = level_cells(pl->levels);
+    uint32_t *slot = pl->phi_nf.as<uint32_t>();  // the near field writes this array later
     stage_begin(pl, FMM_STAGE_TOTAL);
     stage_begin(pl, FMM_STAGE_SORT);
-    HIPCHK(pl, launch_fill_u32(pl->count.as<uint32_t>(), 0u, nleaf, s), "fill");
-    HIPCHK(pl, launch_fill_u32(pl->cursor.as<uint32_t>(), 0u, nleaf, s), "fill");
-    HIPCHK(pl, launch_fill_u32(pl->flag.as<uint32_t>(), 0u, 4, s), "fill");
-    HIPCHK(pl, launch_bin(n, pos, q, pl->box, pl->levels, pl->key.as<uint32_t>(), pl->count.as<uint32_t>(),
+    HIPCHK(pl, launch_sort_begin(pl->count.as<uint32_t>(), nleaf, pl->flag.as<int>(), s), "sort");
+    HIPCHK(pl, launch_bin(n, pos, q, pl->box, pl->levels, pl->key.as<uint32_t>(), slot, pl->count.as<uint32_t>(),
                           pl->flag.as<int>(), s), "bin");
-    HIPCHK(pl, launch_scan(pl->count.as<uint32_t>(), pl->start.as<int32_t>(), nleaf, pl->scan.as<int32_t>(),
-                           scan_scratch_len(nleaf), s), "scan");
-    HIPCHK(pl, launch_scatter(n, pl->key.as<uint32_t>(), pl->start.as<int32_t>(), pl->cursor.as<uint32_t>(),
-                              pl->perm.as<int32_t>(), s), "scatter");
-    HIPCHK(pl, launch_cell_sort(nleaf, pl->start.as<int32_t>(), pl->perm.as<int32_t>(), s), "cell sort");
+    HIPCHK(pl, launch_leaf_ranges(pl->count.as<uint32_t>(), nleaf, plan_groups(pl, n), pl->start.as<int32_t>(),
+                                  pl->pstart.as<int32_t>(), pl->cursor.as<uint32_t>(), pl->scan.as<int32_t>(),
+                                  scan_scratch_len(nleaf), s), "scan");
+    HIPCHK(pl, launch_scatter(n, pl->key.as<uint32_t>(), slot, pl->start.as<int32_t>(), pl->perm.as<int32_t>(), s),
+           "scatter");
     stage_end(pl, FMM_STAGE_SORT);
     return FMM_OK;
 }
@@ -1027,34 +1037,22 @@ static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *ph
     return FMM_OK;
 }
 
-static int p2p_groups(int64_t n, int levels) {
-    // 4 groups of 16 target slots fit the 10-40 atom leaves of water boxes at
-    // 4-7 A leaf edges best (measured: 30 atoms/leaf G 4 < 2 < 8; 11 atoms/leaf
-    // G 4 < 8); sparse leaves take more groups, crowded ones fewer
-    const double occ = (double)n / (double)level_cells(levels);
-    if (occ > 48.0) return 2;
-    if (occ > 5.0) return 4;
-    if (occ > 2.5) return 8;
-    return 16;
-}
-
 template <typename T>
 static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const double *q) {
     hipStream_t s = pl->stream;
     fmm_status st;
     if ((st = sort_atoms(pl, n, pos, q)) != FMM_OK) return st;
     stage_begin(pl, FMM_STAGE_GATHER);
-    HIPCHK(pl, launch_gather(n, pl->perm.as<int32_t>(), pos, q, pl->box, pl->levels, pl->prec == FMM_FP64,
-                             pl->xq.ptr, pl->xs.as<double>(), s), "gather");
+    HIPCHK(pl, launch_sort_gather(level_cells(pl->levels), pl->start.as<int32_t>(), pl->pstart.as<int32_t>(),
+                                  pl->perm.as<int32_t>(), pos, q, pl->box, pl->levels, pl->prec == FMM_FP64,
+                                  16.0 * pl->box, pl->xq.ptr, pl->xs.as<double>(), pl->xqp.ptr, s), "gather");
     stage_end(pl, FMM_STAGE_GATHER);
     // The near field depends only on the sorted atoms: it runs on the plan's
     // side stream concurrently with the upward pass and the upper M2L levels,
     // which leave most of the chip idle (measured on the 1M-atom box: forking
     // here saves 0.85 ms per step, forking after M2M none); the main stream
-    // joins it before the corrections.  The side stream first builds the near-field
-    // copy with leaves padded to a multiple of the P2P group count (the sort's
-    // cursor array is free again and holds the padded counts).  Plans of a
-    // batch keep the near field on their own stream: a batch is already one
+    // joins it before the corrections.  The moments of the corrections follow
+    // there, off the far field's chain.  Plans of a batch keep the near field on their own stream: a batch is already one
     // parallel graph branch per box, and the nested fork inside a captured
     // graph is not used (one such run ended in a host-side crash).
     const bool fork = !pl->in_batch;
@@ -1066,14 +1064,9 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
             HIPCHK(pl, hipStreamWaitEvent(ns, pl->ev_fork, 0), "stream wait");
         }
         const int64_t nleaf = level_cells(pl->levels);
-        const int groups = pl->p2p_g ? pl->p2p_g : p2p_groups(n, pl->levels);
+        const int groups = plan_groups(pl, n);
         const double h_leaf = pl->box / (double)(1 << pl->levels);
         stage_begin(pl, FMM_STAGE_P2P, ns);
-        HIPCHK(pl, launch_pad_counts(nleaf, pl->count.as<uint32_t>(), groups, pl->cursor.as<uint32_t>(), ns), "pad");
-        HIPCHK(pl, launch_scan(pl->cursor.as<uint32_t>(), pl->pstart.as<int32_t>(), nleaf, pl->scan.as<int32_t>(),
-                               scan_scratch_len(nleaf), ns), "scan");
-        HIPCHK(pl, launch_pad_gather(nleaf, pl->start.as<int32_t>(), pl->pstart.as<int32_t>(), pl->prec == FMM_FP64,
-                                     pl->xq.ptr, 16.0 * pl->box, pl->xqp.ptr, ns), "pad gather");
         // target chunks of TS = 64 / groups atoms; enough wavefronts per leaf
         // to cover the mean occupancy once, and at least 64k wavefronts
         const double occ = (double)n / (double)nleaf;
@@ -1086,6 +1079,8 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
                                  n + (int64_t)groups * nleaf, ns),
                "P2P");
         stage_end(pl, FMM_STAGE_P2P, ns);
+        HIPCHK(pl, launch_moments(n, pl->xs.as<double>(), pl->partials.as<double>(), moments_blocks(n),
+                                  pl->scalars.as<double>(), pl->flag.as<int>() + 1, ns), "moments");
         if (fork) HIPCHK(pl, hipEventRecord(pl->ev_join, ns), "event record");
         return FMM_OK;
     };
@@ -1126,28 +1121,24 @@ static fmm_status finish_readback(fmm_plan_t pl, int nscalars) {
     return check_readback(pl);
 }
 
-// All device work of one evaluation plus the readback copies, enqueued on the
-// plan stream without synchronising (also used under stream capture).
+// All device work of one evaluation, the host's scalars included, enqueued on
+// the plan stream without synchronising.
 template <typename T>
 static fmm_status enqueue_energy_forces(fmm_plan_t pl, int64_t n, const double *pos, const double *q,
                                         double *forces, double *phi) {
     hipStream_t s = pl->stream;
     fmm_status st;
     if ((st = run_fields<T>(pl, n, pos, q)) != FMM_OK) return st;
-    const int nb = moments_blocks(n);
-    double *sc = pl->scalars.as<double>();
     stage_begin(pl, FMM_STAGE_FINAL);
-    HIPCHK(pl, launch_moments(n, pl->xs.as<double>(), pl->perm.as<int32_t>(), nullptr, 0, pl->partials.as<double>(),
-                              nb, sc, s), "moments");
-    HIPCHK(pl, hipMemcpyAsync(sc + 10, pl->M0.ptr, sizeof(double), hipMemcpyDeviceToDevice, s), "copy");
     HIPCHK(pl, launch_finalize<T>(n, pl->perm.as<int32_t>(), pl->xs.as<double>(), pl->box, pl->kappa,
-                                  pl->t00 / pl->box, pl->boundary == FMM_BOUNDARY_VACUUM ? 0.0 : 1.0, sc,
-                                  pl->M0.as<double>(), pl->phi_nf.as<double>(),
+                                  pl->t00 / pl->box, pl->boundary == FMM_BOUNDARY_VACUUM ? 0.0 : 1.0,
+                                  pl->scalars.as<double>(), pl->M0.as<double>(), pl->phi_nf.as<double>(),
                                   pl->field_nf.as<T>(), pl->phi_ff.as<double>(), pl->field_ff.as<T>(), forces, phi,
-                                  pl->partials.as<double>(), nb, sc + 8, s), "finalize");
+                                  pl->partials.as<double>(), moments_blocks(n), pl->flag.as<int>(), pl->h_scalars,
+                                  kScalars - 1, s), "finalize");
     stage_end(pl, FMM_STAGE_FINAL);
     stage_end(pl, FMM_STAGE_TOTAL);
-    return enqueue_readback(pl, 11);
+    return FMM_OK;  // the last kernel has written the host's scalars
 }
 
 // after the plan stream has been synchronised
@@ -1264,8 +1255,6 @@ static fmm_status parts_t(fmm_plan_t pl, int64_t n, const double *pos, const dou
     fmm_status st;
     if ((st = run_fields<T>(pl, n, pos, q)) != FMM_OK) return st;
     double *sc = pl->scalars.as<double>();
-    HIPCHK(pl, launch_moments(n, pl->xs.as<double>(), pl->perm.as<int32_t>(), nullptr, 0, pl->partials.as<double>(),
-                              moments_blocks(n), sc, s), "moments");
     HIPCHK(pl, launch_parts_out<T>(n, pl->perm.as<int32_t>(), pl->phi_nf.as<double>(), pl->field_nf.as<T>(),
                                    pl->M0.as<double>(), 0.0, phi_nf, field_nf, s), "parts");
     // the far field includes the net-charge lattice constant t00 Q_tree / b
@@ -1599,6 +1588,7 @@ extern "C" fmm_status fmm_bin(fmm_plan_t pl, int64_t n, const double *pos, uint3
     hipStream_t s = pl->stream;
     if ((st = sort_atoms(pl, n, pos, nullptr)) != FMM_OK) return st;
     const int64_t nleaf = level_cells(pl->levels);
+    HIPCHK(pl, launch_cell_sort(nleaf, pl->start.as<int32_t>(), pl->perm.as<int32_t>(), s), "cell sort");
     if (keys && n > 0) HIPCHK(pl, hipMemcpyAsync(keys, pl->key.ptr, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s), "copy");
     if (perm && n > 0) HIPCHK(pl, hipMemcpyAsync(perm, pl->perm.ptr, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s), "copy");
     if (cell_start)
@@ -1809,64 +1799,70 @@ static fmm_status check_batch_offsets(fmm_plan_t pl, const int64_t *off) {
     return FMM_OK;
 }
 
-// Capture `enqueue(w)` for every non-empty box as parallel branches of one
-// graph (fork from and join into the batch stream), or reuse the graph that
-// was captured for the same key.  Launches it; the caller synchronises.
-struct NoTail {
-    fmm_status operator()() const { return FMM_OK; }
-};
+// `enqueue(w)` for every non-empty box, each on its own stream, forked from and
+// joined into the batch stream
+template <typename F>
+static fmm_status batch_branches(fmm_plan_t pl, const int64_t *off, F enqueue) {
+    hipStream_t cs = pl->stream;
+    HIPCHK(pl, hipEventRecord(pl->fork, cs), "event record");
+    for (size_t w = 0; w < pl->sub.size(); ++w) {
+        if (off[w + 1] == off[w]) continue;
+        fmm_plan_t b = pl->sub[w];
+        b->stream = pl->sub_stream[w];
+        HIPCHK(pl, hipStreamWaitEvent(b->stream, pl->fork, 0), "stream wait");
+        const fmm_status st = enqueue(w);
+        if (st != FMM_OK) {
+            pl->err = "box " + std::to_string(w) + ": " + b->err;
+            return st;
+        }
+        HIPCHK(pl, hipEventRecord(pl->sub_done[w], b->stream), "event record");
+        HIPCHK(pl, hipStreamWaitEvent(cs, pl->sub_done[w], 0), "stream wait");
+    }
+    return FMM_OK;
+}
 
-// branches: false to capture no per-box branch (only the tail); tail: work
-// enqueued on the batch stream after every branch has joined it
-template <typename F, typename G = NoTail>
-static fmm_status batch_run(fmm_plan_t pl, fmm_plan::Graph &g, const std::vector<int64_t> &key,
-                            const int64_t *off, F enqueue, bool branches = true, G tail = G()) {
+// The plan's own stream does not order itself after the null stream, on which
+// the caller's inputs may still be in flight
+static fmm_status batch_inputs(fmm_plan_t pl) {
+    if (pl->stream != pl->own_stream) return FMM_OK;
+    HIPCHK(pl, hipEventRecord(pl->input_ready, nullptr), "event record");
+    HIPCHK(pl, hipStreamWaitEvent(pl->stream, pl->input_ready, 0), "stream wait");
+    return FMM_OK;
+}
+
+// The solute-solvent pass as one graph, captured for a new key and replayed for
+// the same one: every box's branch (branches true), then tail's work on the
+// batch stream.  The caller synchronises.
+template <typename F, typename G>
+static fmm_status batch_run(fmm_plan_t pl, fmm_plan::Graph &g, const std::vector<int64_t> &key, const int64_t *off,
+                            F enqueue, bool branches, G tail) {
     hipStream_t cs = pl->stream;
     if (!g.exec || g.key != key) {
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
         g.exec = nullptr;
         g.key.clear();
         HIPCHK(pl, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "graph capture");
-        fmm_status st = FMM_OK;
-        hipError_t e = hipEventRecord(pl->fork, cs);
-        for (size_t w = 0; branches && w < pl->sub.size() && st == FMM_OK && e == hipSuccess; ++w) {
-            if (off[w + 1] == off[w]) continue;
-            fmm_plan_t b = pl->sub[w];
-            b->stream = pl->sub_stream[w];
-            e = hipStreamWaitEvent(b->stream, pl->fork, 0);
-            if (e != hipSuccess) break;
-            st = enqueue(w);
-            if (st != FMM_OK) {
-                pl->err = "box " + std::to_string(w) + ": " + b->err;
-                break;
-            }
-            e = hipEventRecord(pl->sub_done[w], b->stream);
-            if (e == hipSuccess) e = hipStreamWaitEvent(cs, pl->sub_done[w], 0);
-        }
-        if (st == FMM_OK && e == hipSuccess) st = tail();
+        fmm_status st = branches ? batch_branches(pl, off, enqueue) : FMM_OK;
+        if (st == FMM_OK) st = tail();
         hipGraph_t graph = nullptr;
         const hipError_t ec = hipStreamEndCapture(cs, &graph);
         if (st != FMM_OK) {
             if (graph) (void)hipGraphDestroy(graph);
             return st;
         }
-        if (e != hipSuccess || ec != hipSuccess) {
+        if (ec != hipSuccess) {
             if (graph) (void)hipGraphDestroy(graph);
-            return hip_fail(pl, e != hipSuccess ? e : ec, "graph capture");
+            return hip_fail(pl, ec, "graph capture");
         }
         hipGraphExec_t exec = nullptr;
-        e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+        const hipError_t e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
         (void)hipGraphDestroy(graph);
         if (e != hipSuccess) return hip_fail(pl, e, "graph instantiate");
         g.exec = exec;
         g.key = key;
     }
-    if (cs == pl->own_stream) {
-        // the plan's own stream does not order itself after the null stream,
-        // on which the caller's inputs may still be in flight
-        HIPCHK(pl, hipEventRecord(pl->input_ready, nullptr), "event record");
-        HIPCHK(pl, hipStreamWaitEvent(cs, pl->input_ready, 0), "stream wait");
-    }
+    const fmm_status st = batch_inputs(pl);
+    if (st != FMM_OK) return st;
     HIPCHK(pl, hipGraphLaunch(g.exec, cs), "graph launch");
     return FMM_OK;
 }
@@ -1892,20 +1888,18 @@ extern "C" fmm_status fmm_energy_forces_batch(fmm_plan_t pl, const int64_t *offs
             return st;
         }
     }
-    std::vector<int64_t> key(offsets, offsets + nb + 1);
-    key.push_back((int64_t)(uintptr_t)pos);
-    key.push_back((int64_t)(uintptr_t)q);
-    key.push_back((int64_t)(uintptr_t)forces);
-    key.push_back(pl->prec);
-    key.push_back(pl->boundary);
-    st = batch_run(pl, pl->g_ef, key, offsets, [&](size_t w) -> fmm_status {
+    if ((st = batch_inputs(pl)) != FMM_OK) return st;
+    st = batch_branches(pl, offsets, [&](size_t w) -> fmm_status {
         fmm_plan_t b = pl->sub[w];
         const int64_t o = offsets[w], n = offsets[w + 1] - o;
         double *f = forces ? forces + 3 * o : nullptr;
         return b->prec == FMM_FP64 ? enqueue_energy_forces<double>(b, n, pos + 3 * o, q + o, f, nullptr)
                                    : enqueue_energy_forces<float>(b, n, pos + 3 * o, q + o, f, nullptr);
     });
-    if (st != FMM_OK) return st;
+    if (st != FMM_OK) {
+        (void)hipDeviceSynchronize();  // boxes already enqueued read the caller's arrays
+        return st;
+    }
     HIPCHK(pl, hipStreamSynchronize(pl->stream), "synchronize");
     for (size_t w = 0; w < nb; ++w) {
         fmm_plan_t b = pl->sub[w];

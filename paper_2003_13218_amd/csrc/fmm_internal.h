@@ -87,21 +87,23 @@ void build_rec_tables(RecTables *t);
 hipError_t upload_rec_tables(const RecTables &t);
 
 // k_sort.hip
-hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
-hipError_t launch_fill_f64(double *p, double v, int64_t n, hipStream_t s);
-hipError_t launch_bin(int64_t n, const double *pos, const double *q, double box, int levels,
-                      uint32_t *key, uint32_t *count, int *flag, hipStream_t s);
-hipError_t launch_scan(const uint32_t *in, int32_t *out_exclusive, int64_t n,
-                       int32_t *scratch, int64_t scratch_len, hipStream_t s);
+// flag[0]: an input is not finite; [1], [2]: blocks of k_moments and
+// k_finalize that have ended (their last one adds the blocks' sums)
+constexpr int kFlags = 4;
+hipError_t launch_sort_begin(uint32_t *count, int64_t nleaf, int *flag, hipStream_t s);
+// slot: n entries of scratch
+hipError_t launch_bin(int64_t n, const double *pos, const double *q, double box, int levels, uint32_t *key,
+                      uint32_t *slot, uint32_t *count, int *flag, hipStream_t s);
 int64_t scan_scratch_len(int64_t n);
-hipError_t launch_scatter(int64_t n, const uint32_t *key, const int32_t *start, uint32_t *cursor,
-                          int32_t *perm, hipStream_t s);
+// exclusive sums of the counts and of the counts rounded up to multiples of G
+hipError_t launch_leaf_ranges(const uint32_t *count, int64_t nleaf, int G, int32_t *start, int32_t *pstart,
+                              uint32_t *pcount, int32_t *scratch, int64_t scratch_len, hipStream_t s);
+hipError_t launch_scatter(int64_t n, const uint32_t *key, const uint32_t *slot, const int32_t *start, int32_t *perm,
+                          hipStream_t s);
 hipError_t launch_cell_sort(int64_t nleaf, const int32_t *start, int32_t *perm, hipStream_t s);
-hipError_t launch_pad_counts(int64_t nleaf, const uint32_t *count, int G, uint32_t *pcount, hipStream_t s);
-hipError_t launch_pad_gather(int64_t nleaf, const int32_t *start, const int32_t *pstart, bool fp64,
-                             const void *xq, double far, void *xqp, hipStream_t s);
-hipError_t launch_gather(int64_t n, const int32_t *perm, const double *pos, const double *q,
-                         double box, int levels, bool fp64, void *xq, double *xs, hipStream_t s);
+hipError_t launch_sort_gather(int64_t nleaf, const int32_t *start, const int32_t *pstart, int32_t *perm,
+                              const double *pos, const double *q, double box, int levels, bool fp64, double far,
+                              void *xq, double *xs, void *xqp, hipStream_t s);
 hipError_t launch_mask_charges(int64_t n, const int32_t *perm, const uint8_t *mask, bool fp64,
                                const void *xq, void *xq_u, hipStream_t s);
 hipError_t launch_invert_mask(int64_t n, const uint8_t *mask, uint8_t *out, hipStream_t s);
@@ -370,16 +372,21 @@ hipError_t launch_p2p(int64_t nleaf, int levels, const void *xqp, const int32_t 
 struct Moments {  // device-side FP64 results of the moment reduction
     double Q, mux, muy, muz, S2;
 };
-hipError_t launch_moments(int64_t n, const double *xs, const int32_t *perm, const uint8_t *mask,
-                          int want, double *partials, int nblocks, double *out5, hipStream_t s);
+// moments of all atoms into out5; done: a zeroed counter
+hipError_t launch_moments(int64_t n, const double *xs, double *partials, int nblocks, double *out5, int *done,
+                          hipStream_t s);
 int moments_blocks(int64_t n);
 // mu_w: weight of the dipole parts of the background terms, 1 under the
-// conducting boundary, 0 under vacuum (the dipole surface term cancels them)
+// conducting boundary, 0 under vacuum (the dipole surface term cancels them).
+// flag: kFlags ints (counter in [2]); host: pinned host mirror, which receives
+// the energy at [8], its pair part at [9], the tree's monopole at [10] and
+// flag[0] as an int at [host_flag]
 template <typename T>
 hipError_t launch_finalize(int64_t n, const int32_t *perm, const double *xs, double box, double kappa,
                            double t00b, double mu_w, const double *moments, const double *m0, const double *phi_nf,
                            const T *field_nf, const double *phi_ff, const T *field_ff, double *forces,
-                           double *phi, double *partials, int nblocks, double *energy_out, hipStream_t s);
+                           double *phi, double *partials, int nblocks, int *flag, double *host, int host_flag,
+                           hipStream_t s);
 template <typename T>
 hipError_t launch_parts_out(int64_t n, const int32_t *perm, const double *phi_s, const T *field_s,
                             const double *m0, double cq, double *phi, double *field, hipStream_t s);

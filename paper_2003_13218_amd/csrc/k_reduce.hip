@@ -60,17 +60,35 @@ int moments_blocks(int64_t n) {
     return (int)b;
 }
 
-// partial sums of (Q, mu_x, mu_y, mu_z, S) over sorted atoms s (xs: wrapped
-// position from the box centre and charge), restricted to atoms whose flag
-// mask[perm[s]] equals `want` when a mask is given
+// Block sums for the block that ends last.  They are stored and read past the
+// caches (agent scope) and only thread 0 writes them, so the wait for its stores
+// orders them before the count; no fence writes the whole L2 back (with
+// __threadfence() instead k_finalize took 145 us on the 1M-atom box, 24 us so).
+__device__ inline void put(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double get(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// done counts the blocks of the launch, from zero
+__device__ inline bool last_block(int *done) {
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    }
+    __syncthreads();
+    return last;
+}
+
+// Sums of (Q, mu_x, mu_y, mu_z, S) over the atoms xs (wrapped position from the
+// box centre and charge): per block, then by the last block in block order.
 __global__ __launch_bounds__(kRedBlock) void k_moments(int64_t n, const double *__restrict__ xs,
-                                                        const int32_t *__restrict__ perm,
-                                                        const uint8_t *__restrict__ mask, int want,
-                                                        double *__restrict__ partials) {
+                                                        double *__restrict__ partials, double *__restrict__ out,
+                                                        int *__restrict__ done) {
     NSum v[5];
     for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n;
          s += (int64_t)gridDim.x * blockDim.x) {
-        if (mask && ((mask[perm[s]] != 0) != (want != 0))) continue;
         const double x = xs[4 * s], y = xs[4 * s + 1], z = xs[4 * s + 2];
         const double qi = xs[4 * s + 3];
         v[0].add(qi);
@@ -82,38 +100,38 @@ __global__ __launch_bounds__(kRedBlock) void k_moments(int64_t n, const double *
     block_reduce<5>(v);
     if (threadIdx.x == 0)
         for (int k = 0; k < 5; ++k) {
-            partials[(blockIdx.x * 5 + k) * 2] = v[k].s;
-            partials[(blockIdx.x * 5 + k) * 2 + 1] = v[k].c;
+            put(partials + (blockIdx.x * 5 + k) * 2, v[k].s);
+            put(partials + (blockIdx.x * 5 + k) * 2 + 1, v[k].c);
         }
-}
-
-template <int NV>
-__global__ __launch_bounds__(kRedBlock) void k_final_sum(const double *__restrict__ partials, int nblocks,
-                                                          double *__restrict__ out) {
-    NSum v[NV];
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x)
-        for (int k = 0; k < NV; ++k) v[k].merge(partials[(b * NV + k) * 2], partials[(b * NV + k) * 2 + 1]);
-    block_reduce<NV>(v);
+    if (!last_block(done)) return;
+    NSum t[5];
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x)
+        for (int k = 0; k < 5; ++k) t[k].merge(get(partials + (b * 5 + k) * 2), get(partials + (b * 5 + k) * 2 + 1));
+    block_reduce<5>(t);
     if (threadIdx.x == 0)
-        for (int k = 0; k < NV; ++k) out[k] = v[k].value();
+        for (int k = 0; k < 5; ++k) out[k] = t[k].value();
 }
 
-hipError_t launch_moments(int64_t n, const double *xs, const int32_t *perm, const uint8_t *mask, int want,
-                          double *partials, int nblocks, double *out5, hipStream_t s) {
-    hipLaunchKernelGGL(k_moments, dim3(nblocks), dim3(kRedBlock), 0, s, n, xs, perm, mask, want, partials);
-    hipLaunchKernelGGL(k_final_sum<5>, dim3(1), dim3(kRedBlock), 0, s, partials, nblocks, out5);
+hipError_t launch_moments(int64_t n, const double *xs, double *partials, int nblocks, double *out5, int *done,
+                          hipStream_t s) {
+    hipLaunchKernelGGL(k_moments, dim3(nblocks), dim3(kRedBlock), 0, s, n, xs, partials, out5, done);
     return hipGetLastError();
 }
 
 // Per sorted atom s (i = perm[s]): total potential and force in the caller's
-// order, and the partial sums of E_pair = 1/2 sum q_i (phi_NF + phi_FF).
+// order, and the partial sums of E_pair = 1/2 sum q_i (phi_NF + phi_FF).  The
+// block that ends last adds them in block order, forms E = E_pair + E_corr and
+// writes the call's scalars to the pinned host mirror itself (small boxes are
+// bound by the number of launches and copies: 3,241 atoms, mixed: 212 us with the sort, these and the near-field copy in 31
+// launches and copies, 168 us in 20).
 template <typename T>
 __global__ __launch_bounds__(kRedBlock) void k_finalize(
     int64_t n, const int32_t *__restrict__ perm, const double *__restrict__ xs,
     double box, double kappa, double t00b, double mu_w, const double *__restrict__ mom,
     const double *__restrict__ m0, const double *__restrict__ phi_nf,
     const T *__restrict__ field_nf, const double *__restrict__ phi_ff, const T *__restrict__ field_ff,
-    double *__restrict__ forces, double *__restrict__ phi_out, double *__restrict__ partials) {
+    double *__restrict__ forces, double *__restrict__ phi_out, double *__restrict__ partials,
+    int *__restrict__ flag, double *__restrict__ host, int host_flag) {
     const double V = box * box * box;
     const double Q = mom[0], mux = mom[1], muy = mom[2], muz = mom[3], S = mom[4];
     // charged-system term (eq. 6) and the net-charge lattice constant
@@ -147,30 +165,25 @@ __global__ __launch_bounds__(kRedBlock) void k_finalize(
     }
     block_reduce<1>(e);
     if (threadIdx.x == 0) {
-        partials[blockIdx.x * 2] = e[0].s;
-        partials[blockIdx.x * 2 + 1] = e[0].c;
+        put(partials + blockIdx.x * 2, e[0].s);
+        put(partials + blockIdx.x * 2 + 1, e[0].c);
     }
-}
-
-// E = E_pair + E_corr
-__global__ __launch_bounds__(kRedBlock) void k_energy_final(const double *__restrict__ partials, int nblocks,
-                                                             const double *__restrict__ mom, double box,
-                                                             double kappa, double t00b, double mu_w,
-                                                             const double *__restrict__ m0, double *__restrict__ out) {
+    if (!last_block(flag + 2)) return;
     NSum v[1];
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) v[0].merge(partials[2 * b], partials[2 * b + 1]);
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x)
+        v[0].merge(get(partials + 2 * b), get(partials + 2 * b + 1));
     block_reduce<1>(v);
     if (threadIdx.x == 0) {
-        const double V = box * box * box;
-        const double Q = mom[0], S = mom[4];
-        const double mu2 = mom[1] * mom[1] + mom[2] * mom[2] + mom[3] * mom[3];
+        const double mu2 = mux * mux + muy * muy + muz * muz;
         NSum t;
         t.merge(v[0].s, v[0].c);
         t.add(-M_PI * Q * Q / (2.0 * V * kappa * kappa));
         t.add(0.5 * t00b * Q * m0[0]);
         t.add(2.0 * M_PI / (3.0 * V) * (Q * S - mu_w * mu2));
-        out[0] = t.value();
-        out[1] = v[0].value();
+        host[8] = t.value();
+        host[9] = v[0].value();
+        host[10] = m0[0];
+        *reinterpret_cast<int *>(host + host_flag) = flag[0];
     }
 }
 
@@ -178,21 +191,19 @@ template <typename T>
 hipError_t launch_finalize(int64_t n, const int32_t *perm, const double *xs, double box, double kappa,
                            double t00b, double mu_w, const double *moments, const double *m0, const double *phi_nf,
                            const T *field_nf, const double *phi_ff, const T *field_ff, double *forces, double *phi,
-                           double *partials, int nblocks, double *energy_out, hipStream_t s) {
+                           double *partials, int nblocks, int *flag, double *host, int host_flag, hipStream_t s) {
     hipLaunchKernelGGL(k_finalize<T>, dim3(nblocks), dim3(kRedBlock), 0, s, n, perm, xs, box, kappa, t00b, mu_w,
-                       moments, m0, phi_nf, field_nf, phi_ff, field_ff, forces, phi, partials);
-    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kRedBlock), 0, s, partials, nblocks, moments, box, kappa,
-                       t00b, mu_w, m0, energy_out);
+                       moments, m0, phi_nf, field_nf, phi_ff, field_ff, forces, phi, partials, flag, host, host_flag);
     return hipGetLastError();
 }
 template hipError_t launch_finalize<float>(int64_t, const int32_t *, const double *, double, double, double, double,
                                            const double *, const double *, const double *, const float *,
-                                           const double *, const float *, double *, double *, double *, int, double *,
-                                           hipStream_t);
+                                           const double *, const float *, double *, double *, double *, int, int *,
+                                           double *, int, hipStream_t);
 template hipError_t launch_finalize<double>(int64_t, const int32_t *, const double *, double, double, double, double,
-                                            const double *, const double *, const double *, const double *, const double *,
-                                            const double *, double *, double *, double *, int, double *,
-                                            hipStream_t);
+                                            const double *, const double *, const double *, const double *,
+                                            const double *, const double *, double *, double *, double *, int, int *,
+                                            double *, int, hipStream_t);
 
 // Sorted-order potential / field to the caller's order in FP64.
 template <typename T>
