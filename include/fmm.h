@@ -130,12 +130,12 @@ fmm_status fmm_plan_config(fmm_plan_t plan, int precision, double kappa, void *h
  *                Ewald sum, 4 gives 7e-7 at about 0.8 ms more per
  *                evaluation.  Ignored in FMM_FP64 (everything is FP64).
  *                -1 keeps the current value.
- *   p2p_groups   source groups of the near-field kernel (1, 2, 4, 8, 16; the
- *                atoms of a leaf are split in that many target chunks of
- *                64 / groups slots), or 0 to choose from the mean leaf
+ *   p2p_groups   source groups of the near-field kernel (1, 2, 4, 8, 16: the
+ *                atoms of a leaf are split in target chunks of at most 128 /
+ *                groups, between 64 and 8), or 0 to choose from the mean leaf
  *                occupancy (default); -1 keeps the current value.  Changes
  *                the schedule only: results are identical up to the order of
- *                FP64 partial sums.
+ *                sums.
  * On a batch plan it applies to every box (fmm_autotune_batch then replaces
  * the group counts).  Clears the cached state used by
  * fmm_solute_solvent_energy.  FMM_ERR_INVALID for other values.

@@ -839,15 +839,18 @@ static fmm_status ensure_workspace(fmm_plan_t pl, int64_t n) {
     return FMM_OK;
 }
 
+// Source groups of the near field: the largest chunk of targets of a wavefront
+// is 128 / groups.  Sparse leaves fit one chunk of 16 or less anyway, and the few
+// fuller ones are best done in one (11 atoms a leaf, 262,144 leaves: 32 targets
+// 3.62 ms, 16 3.74); crowded leaves take 16 (30 a leaf, 32,768 leaves: 2.03 ms, 32
+// 2.10, 8 2.21), and 8 where 16 would leave the chip with fewer than two
+// wavefronts a slot (30 a leaf, 4,096 leaves: 0.50 ms, 16 0.57, 32 0.67; 59 a leaf,
+// 512 leaves, FP64: 0.38, 0.42, 0.52).  A box of a batch takes what it would take
+// alone, for the same results (24 windows of 512 leaves: 5.54, 5.59, 6.98 ms).
 static int p2p_groups(int64_t n, int levels) {
-    // 4 groups of 16 target slots fit the 10-40 atom leaves of water boxes at
-    // 4-7 A leaf edges best (measured: 30 atoms/leaf G 4 < 2 < 8; 11 atoms/leaf
-    // G 4 < 8); sparse leaves take more groups, crowded ones fewer
-    const double occ = (double)n / (double)level_cells(levels);
-    if (occ > 48.0) return 2;
-    if (occ > 5.0) return 4;
-    if (occ > 2.5) return 8;
-    return 16;
+    const double leaves = (double)level_cells(levels), occ = (double)n / leaves;
+    if (occ <= 16.0) return 4;
+    return leaves * std::ceil(occ / 16.0) < 16384.0 ? 16 : 8;
 }
 static int plan_groups(fmm_plan_t pl, int64_t n) { return pl->p2p_g ? pl->p2p_g : p2p_groups(n, pl->levels); }
 
@@ -861,7 +864,7 @@ static fmm_status sort_atoms(fmm_plan_t pl, int64_t n, const double *pos, const 
     HIPCHK(pl, launch_sort_begin(pl->count.as<uint32_t>(), nleaf, pl->flag.as<int>(), s), "sort");
     HIPCHK(pl, launch_bin(n, pos, q, pl->box, pl->levels, pl->key.as<uint32_t>(), slot, pl->count.as<uint32_t>(),
                           pl->flag.as<int>(), s), "bin");
-    HIPCHK(pl, launch_leaf_ranges(pl->count.as<uint32_t>(), nleaf, plan_groups(pl, n), pl->start.as<int32_t>(),
+    HIPCHK(pl, launch_leaf_ranges(pl->count.as<uint32_t>(), nleaf, 4, pl->start.as<int32_t>(),
                                   pl->pstart.as<int32_t>(), pl->cursor.as<uint32_t>(), pl->scan.as<int32_t>(),
                                   scan_scratch_len(nleaf), s), "scan");
     HIPCHK(pl, launch_scatter(n, pl->key.as<uint32_t>(), slot, pl->start.as<int32_t>(), pl->perm.as<int32_t>(), s),
@@ -1067,16 +1070,17 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
         const int groups = plan_groups(pl, n);
         const double h_leaf = pl->box / (double)(1 << pl->levels);
         stage_begin(pl, FMM_STAGE_P2P, ns);
-        // target chunks of TS = 64 / groups atoms; enough wavefronts per leaf
-        // to cover the mean occupancy once, and at least 64k wavefronts
+        // target chunks; enough wavefronts per leaf to cover the mean occupancy
+        // once, and at least 64k wavefronts
+        const int chunk = std::max(8, std::min(64, 128 / groups));
         const double occ = (double)n / (double)nleaf;
-        int nsplit = (int)std::ceil(occ / (64.0 / groups));
+        int nsplit = (int)std::ceil(occ / chunk);
         while (nsplit < 8 && nleaf * nsplit < 65536) nsplit *= 2;
         nsplit = std::max(1, std::min(nsplit, 8));
         while (nsplit > 1 && nleaf * nsplit >= ((int64_t)1 << 31)) nsplit /= 2;  // wavefront ids stay int
         HIPCHK(pl, launch_p2p<T>(nleaf, pl->levels, pl->xqp.ptr, pl->pstart.as<int32_t>(), pl->start.as<int32_t>(),
-                                 h_leaf, pl->phi_nf.as<double>(), pl->field_nf.as<T>(), groups, nsplit, 0,
-                                 n + (int64_t)groups * nleaf, ns),
+                                 h_leaf, pl->phi_nf.as<double>(), pl->field_nf.as<T>(), chunk, nsplit,
+                                 n + (int64_t)kMaxP2PGroups * nleaf, ns),
                "P2P");
         stage_end(pl, FMM_STAGE_P2P, ns);
         HIPCHK(pl, launch_moments(n, pl->xs.as<double>(), pl->partials.as<double>(), moments_blocks(n),

@@ -8,17 +8,21 @@
 // position relative to the target leaf centre is x_j + t h: all FP32
 // arithmetic stays at the scale of a few leaf edges.
 //
-// One wavefront per leaf.  The 64 lanes are split into TS = 64/G target
-// slots x G source groups: lane (a, g) = lane (a G + g) takes target atom a
-// of the current target chunk and the source atoms j = g, g+G, ... of every
-// neighbour leaf.  Sources come from the padded copy xqp, in which every
-// leaf holds a multiple of G atoms (q = 0 padding far away), so all lanes
-// run the same trip count and the loop has no per-lane bounds test.  Each
-// lane sums a leaf's (about n/G) potential terms in the mode's precision
-// and adds that partial to an FP64 total, so rounding never accumulates over
-// the ~125 n terms of a potential; the field terms fall off as 1/r^2 and are
-// summed in the mode's precision.  The G partial sums of a target are
-// combined with cross-lane shuffles at the end.
+// One wavefront per chunk of a leaf's atoms.  The 64 lanes are split into 64/G
+// target slots x G source groups; a lane holds two targets of the chunk and
+// takes the source atoms j = g, g+G, ... of every neighbour leaf.  Sources come
+// from the padded copy xqp, in which every leaf holds a multiple of 4 atoms
+// (q = 0 padding far away).  Each lane sums a leaf's potential terms in the
+// mode's precision and adds that partial to an FP64 total, so rounding never
+// accumulates over the ~125 n terms of a potential; the field terms fall off as
+// 1/r^2 and are summed in the mode's precision.  The G partial sums of a target
+// are combined with cross-lane shuffles at the end.
+//
+// What bounds it: the vector units.  A pair is 13 full-rate instructions and a
+// reciprocal square root (FP32: 2.9 and 8.6 cycles of a SIMD at 2.4 GHz with all
+// operands in vector registers), 3.8e9 pairs in 4.7e9 lane slots on the 1M-atom
+// box: 1.5 ms at that rate, 2.03 ms measured with the loop, the leaf changes and
+// the return path of the source loads beside them.
 #include <type_traits>
 
 #include "fmm_internal.h"
@@ -80,177 +84,201 @@ __device__ inline Vec4<double>::type load_src(__amdgpu_buffer_rsrc_t r, uint32_t
     return Vec4<double>::type{d(a.x, a.y), d(a.z, a.w), d(b.x, b.y), d(b.z, b.w)};
 }
 
-// Potential and field at (ox, oy, oz) from the sources base[g], base[g + G],
-// ... of a leaf holding n (padded) sources starting at base.  n is a multiple
-// of G, or of G / 2 when HALF: then a last half group may remain, whose upper
-// lanes (g >= G / 2) read the same group's lower half again and drop it.
-// SELF: the sources are the target's own leaf; skip source index self_i.
-template <typename T, int G, bool SELF, bool HALF, bool BUF>
-__device__ inline void p2p_leaf(const typename Vec4<T>::type *__restrict__ base, int n, int g, T ox, T oy, T oz,
-                                int self_i, double &ph, T &fx, T &fy, T &fz) {
+// Targets per lane: a source is loaded once for both (one target per lane keeps
+// the return path of the vector memory busier than the vector units; four spill).
+// 1M-atom box, 30 atoms a leaf: FP32 2.18 -> 2.03 ms, FP64 4.37 -> 3.77 ms; 3M
+// atoms, 11 a leaf, FP32: 4.25 -> 3.62 ms.  (Sources held one a lane and handed
+// round by DPP operands instead: 2.32 and 4.39 ms.)
+constexpr int kP2PTargets = 2;
+
+// Potential and field at the targets (ox, oy, oz) from the sources base[g],
+// base[g + G], ... of the n sources of a leaf; the lanes past n drop their last.
+// SELF: the sources are the targets' own leaf; target u skips source self[u].
+template <typename T, int G, bool SELF, bool BUF>
+__device__ inline void p2p_leaf(const typename Vec4<T>::type *__restrict__ base, int n, int g,
+                                const T (&ox)[kP2PTargets], const T (&oy)[kP2PTargets], const T (&oz)[kP2PTargets],
+                                const int (&self)[kP2PTargets], double (&ph)[kP2PTargets], T (&fx)[kP2PTargets],
+                                T (&fy)[kP2PTargets], T (&fz)[kP2PTargets]) {
     using V4 = typename Vec4<T>::type;
-    T pc = 0;
+    T pc[kP2PTargets];
+#pragma unroll
+    for (int u = 0; u < kP2PTargets; ++u) pc[u] = 0;
+    auto pairs = [&](const V4 &b, int i, bool drop) {
+#pragma unroll
+        for (int u = 0; u < kP2PTargets; ++u)
+            p2p_pair<T>(b, ox[u], oy[u], oz[u], drop || (SELF && i == self[u]), pc[u], fx[u], fy[u], fz[u]);
+    };
     const int nk = n / G;
     if constexpr (BUF) {
         static_assert(std::is_same<T, double>::value, "buffer loads of FP64 sources");
         constexpr uint32_t SZ = sizeof(V4);
         const __amdgpu_buffer_rsrc_t r = leaf_rsrc(base, (uint32_t)n * SZ);
         const uint32_t voff = (uint32_t)g * SZ;
-#pragma unroll 4
-        for (int k = 0; k < nk; ++k)
-            p2p_pair<T>(load_src(r, voff, (uint32_t)k * G * SZ), ox, oy, oz, SELF && k * G + g == self_i, pc, fx, fy,
-                        fz);
-        if (HALF && n != nk * G) {  // wave-uniform
-            const bool in = g < G / 2;
-            const int i = nk * G + g - (in ? 0 : G / 2);
-            p2p_pair<T>(load_src(r, (uint32_t)i * SZ, 0u), ox, oy, oz, !in || (SELF && i == self_i), pc, fx, fy, fz);
+#pragma unroll 1
+        for (int k = 0; k < nk; ++k) pairs(load_src(r, voff, (uint32_t)k * G * SZ), k * G + g, false);
+        if (n != nk * G) {  // wave-uniform
+            const int i = nk * G + g;
+            pairs(load_src(r, (uint32_t)min(i, n - 1) * SZ, 0u), i, i >= n);
         }
     } else {
         const V4 *bp = base + g;
-#pragma unroll 4
-        for (int k = 0; k < nk; ++k) p2p_pair<T>(bp[k * G], ox, oy, oz, SELF && k * G + g == self_i, pc, fx, fy, fz);
-        if (HALF && n != nk * G) {  // wave-uniform
-            const bool in = g < G / 2;
-            const int i = nk * G + g - (in ? 0 : G / 2);
-            p2p_pair<T>(base[i], ox, oy, oz, !in || (SELF && i == self_i), pc, fx, fy, fz);
+#pragma unroll 1
+        for (int k = 0; k < nk; ++k) pairs(bp[k * G], k * G + g, false);
+        if (n != nk * G) {  // wave-uniform
+            const int i = nk * G + g;
+            pairs(base[min(i, n - 1)], i, i >= n);
         }
     }
-    ph += (double)pc;
+#pragma unroll
+    for (int u = 0; u < kP2PTargets; ++u) ph[u] += (double)pc[u];
 }
 
-// One chunk of up to 64 / G targets of a leaf (first target tb) against its
+// One chunk of up to 128 / G targets of a leaf (first target tb) against its
 // 125 near-field leaves, G source groups per target; results stored by the
 // lanes of group 0.
-template <typename T, int G, bool HALF, bool BUF>
+template <typename T, int G, bool BUF>
 __device__ inline void p2p_chunk(const typename Vec4<T>::type *__restrict__ X, const int32_t *__restrict__ pstart,
                                  uint32_t cx, uint32_t cy, uint32_t cz, uint32_t nmask, int32_t s0, int32_t cnt,
                                  int32_t p0, int32_t pcnt, int32_t tb, T h, int lane, double *__restrict__ phi,
                                  T *__restrict__ field) {
     using V4 = typename Vec4<T>::type;
+    constexpr int NT = kP2PTargets;
     const int g = lane % G;
-    const int a = lane / G;
-    const int32_t t = tb + a;
-    const int32_t tl = min(t, pcnt - 1);  // lanes past the leaf redo its last slot, unstored
-    const V4 ti = X[p0 + tl];
-    double ph = 0;
-    T fx = 0, fy = 0, fz = 0;
-    p2p_leaf<T, G, true, HALF, BUF>(X + p0, pcnt, g, ti.x, ti.y, ti.z, tl, ph, fx, fy, fz);
+    T tx[NT], ty[NT], tz[NT], fx[NT], fy[NT], fz[NT], oz[NT];
+    double ph[NT];
+    int tl[NT];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        tl[u] = min(tb + lane / G + u * (64 / G), cnt - 1);  // past the leaf: its last atom again, unstored
+        const V4 t = X[p0 + tl[u]];
+        tx[u] = t.x;
+        ty[u] = t.y;
+        tz[u] = t.z;
+        ph[u] = 0;
+        fx[u] = fy[u] = fz[u] = 0;
+    }
+    p2p_leaf<T, G, true, BUF>(X + p0, pcnt, g, tx, ty, tz, tl, ph, fx, fy, fz);
     // The 124 other leaves of the 5^3 block, x slowest.  The image shift of
     // an axis runs through -2h, -h, 0, h, 2h by adding h, and every one of
-    // those sums is exact, so ti - shift is rounded once, as ti - d h is: the
+    // those sums is exact, so t - shift is rounded once, as t - d h is: the
     // innermost leaf costs an add and a subtract instead of three conversions
-    // and multiply-adds, and the compiler unrolls the five leaves of a z row
-    // (1M-atom box, results bit-identical to one flat loop over the 125
-    // offsets: FP32 near field 2.56 -> 2.45 ms, FP64 8.4 -> 5.8 ms).
-    T xs = -(T)kWS * h;
+    // and multiply-adds.
+    T xs = -(T)kWS * h, ox[NT], oy[NT];
     for (int dx = -kWS; dx <= kWS; ++dx, xs += h) {
-        const T ox = ti.x - xs;
         T ys = -(T)kWS * h;
+#pragma unroll
+        for (int u = 0; u < NT; ++u) ox[u] = tx[u] - xs;
         for (int dy = -kWS; dy <= kWS; ++dy, ys += h) {
-            const T oy = ti.y - ys;
             T zs = -(T)kWS * h;
+#pragma unroll
+            for (int u = 0; u < NT; ++u) oy[u] = ty[u] - ys;
             for (int dz = -kWS; dz <= kWS; ++dz, zs += h) {
                 if (dx == 0 && dy == 0 && dz == 0) continue;  // the own leaf: done above
                 const uint32_t sc = morton3((cx + dx) & nmask, (cy + dy) & nmask, (cz + dz) & nmask);
                 const int32_t j0 = pstart[sc];
-                p2p_leaf<T, G, false, HALF, BUF>(X + j0, pstart[sc + 1] - j0, g, ox, oy, ti.z - zs, -1, ph, fx, fy,
-                                                 fz);
+#pragma unroll
+                for (int u = 0; u < NT; ++u) oz[u] = tz[u] - zs;
+                p2p_leaf<T, G, false, BUF>(X + j0, pstart[sc + 1] - j0, g, ox, oy, oz, tl, ph, fx, fy, fz);
             }
         }
     }
 #pragma unroll
-    for (int m = 1; m < G; m <<= 1) {
-        ph += __shfl_xor(ph, m);
-        fx += __shfl_xor(fx, m);
-        fy += __shfl_xor(fy, m);
-        fz += __shfl_xor(fz, m);
-    }
-    if (t < cnt && g == 0) {
-        const int64_t si = s0 + t;
-        phi[si] = ph;
-        field[3 * si + 0] = fx;
-        field[3 * si + 1] = fy;
-        field[3 * si + 2] = fz;
+    for (int u = 0; u < NT; ++u) {
+#pragma unroll
+        for (int m = 1; m < G; m <<= 1) {
+            ph[u] += __shfl_xor(ph[u], m);
+            fx[u] += __shfl_xor(fx[u], m);
+            fy[u] += __shfl_xor(fy[u], m);
+            fz[u] += __shfl_xor(fz[u], m);
+        }
+        const int32_t t = tb + lane / G + u * (64 / G);
+        if (t < cnt && g == 0) {
+            const int64_t si = s0 + t;
+            phi[si] = ph[u];
+            field[3 * si + 0] = fx[u];
+            field[3 * si + 1] = fy[u];
+            field[3 * si + 2] = fz[u];
+        }
     }
 }
 
-template <typename T, int G, bool BUF>
-__global__ __launch_bounds__(256) void k_p2p(int64_t nleaf, int levels, const T *__restrict__ xqp,
-                                             const int32_t *__restrict__ pstart, const int32_t *__restrict__ start,
-                                             T h, double *__restrict__ phi, T *__restrict__ field, int nsplit) {
+// Wavefronts per SIMD that the register count is held to (the two targets' state
+// takes 85 and 122 registers by itself): 8 and 6 measured best, with the source
+// loop not unrolled (two targets are enough independent work; FP64 at 4: 4.07 ms
+// against 3.77).
+template <typename T> constexpr int p2p_waves() { return sizeof(T) == 4 ? 8 : 6; }
+
+// C: largest chunk of targets of a wavefront (64, 32, 16 or 8); what remains of a
+// leaf below half of it runs with twice the source groups, and so on down to 8
+// targets of 16 groups.
+template <typename T, int C, bool BUF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(p2p_waves<T>()))) void k_p2p(
+    int64_t nleaf, int levels, const T *__restrict__ xqp, const int32_t *__restrict__ pstart,
+    const int32_t *__restrict__ start, T h, double *__restrict__ phi, T *__restrict__ field, int nsplit) {
     using V4 = typename Vec4<T>::type;
-    constexpr int TS = 64 / G;
-    // a last chunk of at most TS / 2 targets runs with 2G source groups
-    // (measured on the 1M-atom box: 7% fewer pair slots at G = 4)
-    constexpr bool kHalfTail = G <= 8;
     const int lane = threadIdx.x & 63;
     const uint32_t nmask = (1u << levels) - 1u;
     const V4 *X = reinterpret_cast<const V4 *>(xqp);
     // Work items (leaf, part), wavefront-uniform so that the neighbour walk
     // stays on the scalar unit: the target chunks of a leaf are dealt
     // round-robin to nsplit items so that small boxes still fill the chip.
-    // The grid may be smaller than the item count (each wavefront then takes
-    // every stride-th item).  Capping it so that the far-field kernels of the
-    // other stream keep room on every CU was measured slower on the 1M-atom
-    // box (2 workgroups per CU: P2P 19.7 ms, step 29.7 ms), so the callers
-    // launch the full grid.
     const int64_t nitem = nleaf * nsplit;
-    const int first = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-    const int stride = gridDim.x * 4;
-    for (int64_t wv = first; wv < nitem; wv += stride) {
-        const int64_t leaf = wv / nsplit;
-        const int part = (int)(wv % nsplit);
-        uint32_t cx, cy, cz;
-        demorton3((uint32_t)leaf, cx, cy, cz);
-        const int32_t s0 = start[leaf], cnt = start[leaf + 1] - s0;
-        const int32_t p0 = pstart[leaf], pcnt = pstart[leaf + 1] - p0;
-        for (int32_t tb = part * TS; tb < cnt; tb += nsplit * TS) {
-            if (kHalfTail && cnt - tb <= TS / 2)
-                p2p_chunk<T, (kHalfTail ? 2 * G : G), true, BUF>(X, pstart, cx, cy, cz, nmask, s0, cnt, p0, pcnt, tb, h,
-                                                            lane, phi, field);
-            else
-                p2p_chunk<T, G, false, BUF>(X, pstart, cx, cy, cz, nmask, s0, cnt, p0, pcnt, tb, h, lane, phi,
-                                            field);
-        }
+    const int64_t wv = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (wv >= nitem) return;
+    const int64_t leaf = wv / nsplit;
+    const int part = (int)(wv % nsplit);
+    uint32_t cx, cy, cz;
+    demorton3((uint32_t)leaf, cx, cy, cz);
+    const int32_t s0 = start[leaf], cnt = start[leaf + 1] - s0;
+    const int32_t p0 = pstart[leaf], pcnt = pstart[leaf + 1] - p0;
+    for (int32_t tb = part * C; tb < cnt; tb += nsplit * C) {
+        const int32_t r = cnt - tb;
+        auto run = [&](auto gc) {
+            p2p_chunk<T, decltype(gc)::value, BUF>(X, pstart, cx, cy, cz, nmask, s0, cnt, p0, pcnt, tb, h, lane, phi,
+                                                   field);
+        };
+        if (C >= 64 && r > 32) run(std::integral_constant<int, 2>{});
+        else if (C >= 32 && r > 16) run(std::integral_constant<int, 4>{});
+        else if (C >= 16 && r > 8) run(std::integral_constant<int, 8>{});
+        else run(std::integral_constant<int, 16>{});
     }
 }
 
-// max_wg > 0 caps the grid (the kernel loops over the remaining items);
 // nsrc_max bounds the padded source count (buffer loads need every leaf's
 // byte size and offsets below 2^31)
 template <typename T>
 hipError_t launch_p2p(int64_t nleaf, int levels, const void *xqp, const int32_t *pstart, const int32_t *start,
-                      double h, double *phi, T *field, int groups, int nsplit, int max_wg, int64_t nsrc_max,
-                      hipStream_t s) {
+                      double h, double *phi, T *field, int chunk, int nsplit, int64_t nsrc_max, hipStream_t s) {
     if (nsplit < 1 || nsplit > 64) return hipErrorInvalidValue;
-    int64_t grid = (nleaf * nsplit + 3) / 4;
-    if (max_wg > 0 && grid > max_wg) grid = max_wg;
+    const dim3 grid((unsigned)((nleaf * nsplit + 3) / 4));
     const T *x = (const T *)xqp;
     const bool buf = std::is_same<T, double>::value && nsrc_max >= 0 &&
                      nsrc_max * (int64_t)sizeof(typename Vec4<T>::type) < ((int64_t)1 << 31);
-    switch (groups) {
-#define FMM_P2P_CASE(G)                                                                                        \
-    case G:                                                                                                    \
-        if constexpr (std::is_same<T, double>::value) {                                                        \
-            if (buf) {                                                                                         \
-                hipLaunchKernelGGL((k_p2p<T, G, true>), dim3((unsigned)grid), dim3(256), 0, s, nleaf, levels, x, \
-                                   pstart, start, (T)h, phi, field, nsplit);                                   \
-                break;                                                                                         \
-            }                                                                                                  \
-        }                                                                                                      \
-        hipLaunchKernelGGL((k_p2p<T, G, false>), dim3((unsigned)grid), dim3(256), 0, s, nleaf, levels, x,      \
-                           pstart, start, (T)h, phi, field, nsplit);                                           \
-        break;
-        FMM_P2P_CASE(1) FMM_P2P_CASE(2) FMM_P2P_CASE(4) FMM_P2P_CASE(8) FMM_P2P_CASE(16)
-#undef FMM_P2P_CASE
+    auto go = [&](auto cc) {
+        constexpr int C = decltype(cc)::value;
+        if constexpr (std::is_same<T, double>::value) {
+            if (buf) {
+                hipLaunchKernelGGL((k_p2p<T, C, true>), grid, dim3(256), 0, s, nleaf, levels, x, pstart, start, (T)h,
+                                   phi, field, nsplit);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_p2p<T, C, false>), grid, dim3(256), 0, s, nleaf, levels, x, pstart, start, (T)h, phi,
+                           field, nsplit);
+    };
+    switch (chunk) {
+        case 64: go(std::integral_constant<int, 64>{}); break;
+        case 32: go(std::integral_constant<int, 32>{}); break;
+        case 16: go(std::integral_constant<int, 16>{}); break;
+        case 8: go(std::integral_constant<int, 8>{}); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 template hipError_t launch_p2p<float>(int64_t, int, const void *, const int32_t *, const int32_t *, double,
-                                      double *, float *, int, int, int, int64_t, hipStream_t);
+                                      double *, float *, int, int, int64_t, hipStream_t);
 template hipError_t launch_p2p<double>(int64_t, int, const void *, const int32_t *, const int32_t *, double,
-                                       double *, double *, int, int, int, int64_t, hipStream_t);
+                                       double *, double *, int, int, int64_t, hipStream_t);
 
 // Near-field solute-solvent pairs: nfuv[s] = q_s sum_{j in NF(s), solvent} q_j / r
 // for the solute atoms s (ms[s] != 0; entries of solvent atoms are not
