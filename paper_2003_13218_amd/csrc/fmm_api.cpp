@@ -893,8 +893,12 @@ static fmm_status ensure_side_streams(fmm_plan_t pl) {
     return FMM_OK;
 }
 
-template <typename T>
-static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *phi, T *field) {
+// beside(): work for another stream, enqueued once the P2M is
+struct Nothing {
+    fmm_status operator()() const { return FMM_OK; }
+};
+template <typename T, typename F = Nothing>
+static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *phi, T *field, F beside = F()) {
     hipStream_t s = pl->stream;
     const int L = pl->levels, p = pl->p, Kp = pl->Kp;
     const int top = top_fp64_levels(pl);
@@ -915,6 +919,8 @@ static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *ph
     stage_begin(pl, FMM_STAGE_P2M);
     HIPCHK(pl, launch_p2m<T>(level_cells(L), xq, pl->start.as<int32_t>(), MT(L), p, Kp, 1.0 / h_leaf, s), "P2M");
     stage_end(pl, FMM_STAGE_P2M);
+    fmm_status st = beside();
+    if (st != FMM_OK) return st;
     // Levels 1..lup (the upper tree: M2M, the level-0 lattice operator, M2L)
     // run on the second side stream once the M2M has produced level lup + 1,
     // beside the M2L of the two finest levels on the plan stream (not inside a
@@ -1062,10 +1068,7 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
     if (fork && !pl->side) return fail(pl, FMM_ERR_STATE, "plan has no side stream for the near field");
     hipStream_t ns = fork ? pl->side : s;
     auto near_field = [&]() -> fmm_status {
-        if (fork) {
-            HIPCHK(pl, hipEventRecord(pl->ev_fork, s), "event record");
-            HIPCHK(pl, hipStreamWaitEvent(ns, pl->ev_fork, 0), "stream wait");
-        }
+        if (fork) HIPCHK(pl, hipStreamWaitEvent(ns, pl->ev_fork, 0), "stream wait");
         const int64_t nleaf = level_cells(pl->levels);
         const int groups = plan_groups(pl, n);
         const double h_leaf = pl->box / (double)(1 << pl->levels);
@@ -1088,8 +1091,13 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
         if (fork) HIPCHK(pl, hipEventRecord(pl->ev_join, ns), "event record");
         return FMM_OK;
     };
-    if ((st = near_field()) != FMM_OK) return st;
-    if ((st = far_field<T>(pl, n, pl->xq.ptr, pl->phi_ff.as<double>(), pl->field_ff.as<T>())) != FMM_OK) return st;
+    // The near field is enqueued after the P2M: started before it, it takes every
+    // wavefront slot of the chip and the P2M waits for most of its duration
+    // (30,001 atoms: P2M 95 us instead of 21).  Both need the sorted atoms only,
+    // so its fork is recorded first.
+    if (fork) HIPCHK(pl, hipEventRecord(pl->ev_fork, s), "event record");
+    if ((st = far_field<T>(pl, n, pl->xq.ptr, pl->phi_ff.as<double>(), pl->field_ff.as<T>(), near_field)) != FMM_OK)
+        return st;
     if (fork) HIPCHK(pl, hipStreamWaitEvent(s, pl->ev_join, 0), "stream wait");
     return FMM_OK;
 }
