@@ -431,13 +431,17 @@ __device__ inline void conv_product(const ConvLevel &v, int o, int rt, int NB, c
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[w][t][r][lane] = acc[t][r];
     __syncthreads();
-    if (col >= ncol) return;
-    const uint32_t yo = (col0 * NB + rt * ncol) * 128u + (uint32_t)col * 16u;
+    // lanes along the rows: 16 neighbouring results a column
+    const int row = lane & 15;
+    constexpr bool F = sizeof(T) == 4;  // where the result layouts put (row, column)
+    const int rr = F ? row & 3 : row >> 2, rl = 16 * (F ? row >> 2 : row & 3);
+    T *yo = Y + (col0 * NB + rt * ncol) * 128u + row;
     for (int i = w; i < 32; i += nw) {
-        const int t = i >> 2, r = i & 3;
+        const int t = i >> 2, c = 4 * (i & 3) + (lane >> 4);
+        if (c >= ncol) continue;
         double s = 0.0;
-        for (int k = 0; k < nw; ++k) s += red[k][t][r][lane];
-        Y[yo + (uint32_t)t * ncol * 16u + Mfma<T>::row(lane, r)] = (T)s;
+        for (int k = 0; k < nw; ++k) s += red[k][t][rr][rl + c];
+        yo[(uint32_t)(t * ncol + c) * 16u] = (T)s;
     }
 }
 
@@ -446,7 +450,8 @@ __device__ inline void conv_product(const ConvLevel &v, int o, int rt, int NB, c
 // columns and either blocks, by level.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_conv_product(ConvBatch bt, int NB, int swapPQ) {
-    __shared__ double red[4][8][4][64];
+    extern __shared__ double red_raw[];  // [wavefronts][8][4][64]
+    double(*red)[8][4][64] = reinterpret_cast<double(*)[8][4][64]>(red_raw);
     int w = 0;
     while (w + 1 < bt.nlv && (int)blockIdx.x >= bt.start[w + 1]) ++w;
     const ConvLevel &v = bt.lv[w];
@@ -542,13 +547,34 @@ hipError_t launch_conv_build(int level, int p, const double *reps, const int32_t
 
 static int product_blocks(int level, int NB) { return (conv_orbits(level) + 7) / 8 * 8 * NB; }
 
+// Wavefronts of a workgroup: they share the chunks of its rows, and the chip takes
+// 2048 at a time (two a SIMD); of 4, 2 and 1 the number that needs the fewest
+// chunk times in whole rounds (3M-atom box, p = 8, 6 chunks: 2 wavefronts, since 4
+// would leave two of them idle in the second turn: level 6 730 -> 716 us).
+static int product_waves(const ConvBatch &b, int NB) {
+    int64_t tiles = 0, best = 0;
+    int nw = 1;
+    for (int i = 0; i < b.nlv; ++i) tiles += (int64_t)conv_orbits(b.lv[i].level) * NB;
+    for (int k : {4, 2, 1}) {
+        if (k > NB) continue;
+        const int64_t cost = (tiles * k + 2047) / 2048 * ((NB + k - 1) / k);
+        if (best == 0 || cost < best) {
+            best = cost;
+            nw = k;
+        }
+    }
+    return nw;
+}
+
 static hipError_t launch_product(const ConvBatch &b, int blocks, int NB, int swapPQ, hipStream_t s) {
     bool f32 = false;
     for (int i = 0; i < b.nlv; ++i) f32 = f32 || !b.lv[i].fp64;
-    const dim3 grid(blocks), block(64 * (NB < 4 ? NB : 4));
-    if (!f32) hipLaunchKernelGGL(k_conv_product<1>, grid, block, 0, s, b, NB, swapPQ);
-    else if (b.lv[0].level > 4) hipLaunchKernelGGL(k_conv_product<0>, grid, block, 0, s, b, NB, swapPQ);
-    else hipLaunchKernelGGL(k_conv_product<2>, grid, block, 0, s, b, NB, swapPQ);
+    const int nw = product_waves(b, NB);
+    const dim3 grid(blocks), block(64 * nw);
+    const size_t lds = sizeof(double) * nw * 8 * 4 * 64;
+    if (!f32) hipLaunchKernelGGL(k_conv_product<1>, grid, block, lds, s, b, NB, swapPQ);
+    else if (b.lv[0].level > 4) hipLaunchKernelGGL(k_conv_product<0>, grid, block, lds, s, b, NB, swapPQ);
+    else hipLaunchKernelGGL(k_conv_product<2>, grid, block, lds, s, b, NB, swapPQ);
     return hipGetLastError();
 }
 

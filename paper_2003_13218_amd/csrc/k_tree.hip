@@ -10,6 +10,11 @@
 // wavefront keeps the dependent MFMA chain short (K/4 steps) and gives the
 // small upper levels (1 to 512 parents) enough wavefronts to hide latency.
 //
+// The expansions are the rows and the operators the columns of the product (the
+// two operand layouts are alike), so that a lane group of the result holds 16
+// neighbouring coefficients of a cell and the locals are merged in whole lines
+// (3M-atom box, p = 8, into level 6: 245 -> 207 us).
+//
 // Operators are stored in the lane order of v_mfma_*_16x16x4 (the same
 // swizzle as the M2L operators) and stay L2-resident (16 matrices).  All
 // row blocks of one parent block are placed on the same XCD (blockIdx mod 8)
@@ -71,7 +76,7 @@ __global__ __launch_bounds__(512) void k_tree(const typename TreeCompute<Tin, To
         const V b = load_frag<T, Tin>(src + 16 * kc);
         const V a = *reinterpret_cast<const V *>(ap + (size_t)kc * NB * 256);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = Mfma<T>::mma(a[j], b[j], acc);
+        for (int j = 0; j < 4; ++j) acc = Mfma<T>::mma(b[j], a[j], acc);
     }
     if constexpr (M2M) {
 #pragma unroll
@@ -82,13 +87,14 @@ __global__ __launch_bounds__(512) void k_tree(const typename TreeCompute<Tin, To
         double v = 0.0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) v += red[k][r][lane];
-        if (valid) out[P * Kp + 16 * rb + Mfma<T>::row(lane, r)] = (Tout)v;
+        const int64_t Pr = pblk * 16 + Mfma<T>::row(lane, r);
+        if (Pr < nparent) out[Pr * Kp + 16 * rb + (lane & 15)] = (Tout)v;
     } else {
-        if (!valid) return;
-        Tout *dst = out + (8 * P + o) * Kp + 16 * rb;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            Tout *d = dst + Mfma<T>::row(lane, r);
+            const int64_t Pr = pblk * 16 + Mfma<T>::row(lane, r);
+            if (Pr >= nparent) continue;
+            Tout *d = out + (8 * Pr + o) * Kp + 16 * rb + (lane & 15);
             *d = (Tout)((double)*d + (double)acc[r]);  // merge into the M2L result
         }
     }
