@@ -212,7 +212,7 @@ template <typename T> constexpr int p2p_waves() { return sizeof(T) == 4 ? 8 : 6;
 // leaf below half of it runs with twice the source groups, and so on down to 8
 // targets of 16 groups.
 template <typename T, int C, bool BUF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(p2p_waves<T>()))) void k_p2p(
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(p2p_waves<T>()))) void k_p2p(
     int64_t nleaf, int levels, const T *__restrict__ xqp, const int32_t *__restrict__ pstart,
     const int32_t *__restrict__ start, T h, double *__restrict__ phi, T *__restrict__ field, int nsplit) {
     using V4 = typename Vec4<T>::type;
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(p2p_waves<T
     // stays on the scalar unit: the target chunks of a leaf are dealt
     // round-robin to nsplit items so that small boxes still fill the chip.
     const int64_t nitem = nleaf * nsplit;
-    const int64_t wv = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    const int64_t wv = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     if (wv >= nitem) return;
     const int64_t leaf = wv / nsplit;
     const int part = (int)(wv % nsplit);
@@ -244,13 +244,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(p2p_waves<T
     }
 }
 
+// Wavefronts of a workgroup.  The near field fills every wavefront slot of the
+// chip while the far field runs beside it, and a slot that falls free goes to
+// whichever waiting workgroup fits.  Workgroups of the far field take 8 or 16
+// wavefronts of one unit at once and never fit where 4 leave together: up to
+// 4,096 leaves, where the far field's chain of small launches is as long as the
+// near field, 8 leave together and let them in (125,001 atoms, levels 4: whole
+// call 707 -> 571 us; 30,001 atoms 383 -> 339 us; with 16: 622 and 361 us).  Above,
+// the near field or the memory-bound convolution is the longer, and 4 keep the
+// slots fuller (1M atoms, levels 5: 2.88 ms against 3.03; 3M, levels 6: 5.96
+// against 6.37).  The split into wavefronts and with it every sum is the same.
+static int p2p_block_waves(int levels) { return levels <= 4 ? 8 : 4; }
+
 // nsrc_max bounds the padded source count (buffer loads need every leaf's
 // byte size and offsets below 2^31)
 template <typename T>
 hipError_t launch_p2p(int64_t nleaf, int levels, const void *xqp, const int32_t *pstart, const int32_t *start,
                       double h, double *phi, T *field, int chunk, int nsplit, int64_t nsrc_max, hipStream_t s) {
     if (nsplit < 1 || nsplit > 64) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((nleaf * nsplit + 3) / 4));
+    const int bw = p2p_block_waves(levels);
+    const dim3 grid((unsigned)((nleaf * nsplit + bw - 1) / bw)), block(64 * bw);
     const T *x = (const T *)xqp;
     const bool buf = std::is_same<T, double>::value && nsrc_max >= 0 &&
                      nsrc_max * (int64_t)sizeof(typename Vec4<T>::type) < ((int64_t)1 << 31);
@@ -258,12 +271,12 @@ hipError_t launch_p2p(int64_t nleaf, int levels, const void *xqp, const int32_t 
         constexpr int C = decltype(cc)::value;
         if constexpr (std::is_same<T, double>::value) {
             if (buf) {
-                hipLaunchKernelGGL((k_p2p<T, C, true>), grid, dim3(256), 0, s, nleaf, levels, x, pstart, start, (T)h,
+                hipLaunchKernelGGL((k_p2p<T, C, true>), grid, block, 0, s, nleaf, levels, x, pstart, start, (T)h,
                                    phi, field, nsplit);
                 return;
             }
         }
-        hipLaunchKernelGGL((k_p2p<T, C, false>), grid, dim3(256), 0, s, nleaf, levels, x, pstart, start, (T)h, phi,
+        hipLaunchKernelGGL((k_p2p<T, C, false>), grid, block, 0, s, nleaf, levels, x, pstart, start, (T)h, phi,
                            field, nsplit);
     };
     switch (chunk) {
