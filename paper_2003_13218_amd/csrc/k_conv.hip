@@ -241,20 +241,24 @@ struct ConvBatch {
     int start[kConvMaxBatch + 1];  // first block of each level
 };
 
-// DEEP: level 4 among the levels (139 KB of LDS instead of 74)
+// DEEP: level 4 among the levels (70 KB of LDS instead of 37).  512 threads: twice the
+// blocks of 1024 threads, which are few (p = 10: 66 with level 4), and a workgroup
+// that finds room beside the near field's own of 8 wavefronts (leaf M2L of levels 4,
+// p = 10: 137 -> 129 us, levels 3, p = 8: 47 -> 43 us; whole call of 125,001 atoms
+// 577 -> 551 us).
 template <bool FWD, bool DEEP>
-__global__ __launch_bounds__(1024) void k_conv_cube(ConvBatch bt, int NB, int Kp, const ConvCoef *__restrict__ tab) {
-    __shared__ double lds[DEEP ? 16 * 16 * (16 * 4 + 4) : 8 * 8 * (8 * 16 + 16)];
+__global__ __launch_bounds__(512) void k_conv_cube(ConvBatch bt, int NB, int Kp, const ConvCoef *__restrict__ tab) {
+    __shared__ double lds[DEEP ? 16 * 16 * (16 * 2 + 2) : 8 * 8 * (8 * 8 + 8)];
     int w = 0;
     while (w + 1 < bt.nlv && (int)blockIdx.x >= bt.start[w + 1]) ++w;
     const ConvLevel &v = bt.lv[w];
     const int part = blockIdx.x - bt.start[w];
     switch (v.level) {
-        case 1: cube<2, 16, FWD>(v, part, NB, Kp, tab, lds); break;
-        case 2: cube<4, 16, FWD>(v, part, NB, Kp, tab, lds); break;
-        case 3: cube<8, 16, FWD>(v, part, NB, Kp, tab, lds); break;
+        case 1: cube<2, 8, FWD>(v, part, NB, Kp, tab, lds); break;
+        case 2: cube<4, 8, FWD>(v, part, NB, Kp, tab, lds); break;
+        case 3: cube<8, 8, FWD>(v, part, NB, Kp, tab, lds); break;
         case 4:
-            if constexpr (DEEP) cube<16, 4, FWD>(v, part, NB, Kp, tab, lds);
+            if constexpr (DEEP) cube<16, 2, FWD>(v, part, NB, Kp, tab, lds);
             break;
     }
 }
@@ -614,16 +618,16 @@ hipError_t launch_conv(const ConvLevel *lv, int nlv, int p, const ConvCoef *tab,
         if (l < 1 || l > 4) return hipErrorInvalidValue;
         cube.lv[i] = prod.lv[i] = lv[i];
         deep = deep || l == 4;
-        cube.start[i + 1] = cube.start[i] + (l == 4 ? Kp / 4 : NB);
+        cube.start[i + 1] = cube.start[i] + Kp / (l == 4 ? 2 : 8);
         prod.start[i + 1] = prod.start[i] + product_blocks(l, NB);
     }
     const dim3 grid(cube.start[nlv]);
-    if (deep) hipLaunchKernelGGL((k_conv_cube<true, true>), grid, dim3(1024), 0, s, cube, NB, Kp, tab);
-    else hipLaunchKernelGGL((k_conv_cube<true, false>), grid, dim3(1024), 0, s, cube, NB, Kp, tab);
+    if (deep) hipLaunchKernelGGL((k_conv_cube<true, true>), grid, dim3(512), 0, s, cube, NB, Kp, tab);
+    else hipLaunchKernelGGL((k_conv_cube<true, false>), grid, dim3(512), 0, s, cube, NB, Kp, tab);
     hipError_t e = launch_product(prod, prod.start[nlv], NB, 0, s);
     if (e != hipSuccess) return e;
-    if (deep) hipLaunchKernelGGL((k_conv_cube<false, true>), grid, dim3(1024), 0, s, cube, NB, Kp, tab);
-    else hipLaunchKernelGGL((k_conv_cube<false, false>), grid, dim3(1024), 0, s, cube, NB, Kp, tab);
+    if (deep) hipLaunchKernelGGL((k_conv_cube<false, true>), grid, dim3(512), 0, s, cube, NB, Kp, tab);
+    else hipLaunchKernelGGL((k_conv_cube<false, false>), grid, dim3(512), 0, s, cube, NB, Kp, tab);
     return hipGetLastError();
 }
 
