@@ -49,7 +49,7 @@ template <typename T> struct Vec4 { typedef T type __attribute__((ext_vector_typ
 // One source-target pair: potential and field terms of source b at
 // (ox, oy, oz); SKIP drops the pair (the target itself, or a zero lane).
 template <typename T>
-__device__ inline void p2p_pair(const typename Vec4<T>::type &b, T ox, T oy, T oz, bool skip, T &pc, T &fx, T &fy,
+__device__ __forceinline__ void p2p_pair(const typename Vec4<T>::type &b, T ox, T oy, T oz, bool skip, T &pc, T &fx, T &fy,
                                 T &fz) {
     const T dx = ox - b.x, dy = oy - b.y, dz = oz - b.z;
     const T r2 = dx * dx + dy * dy + dz * dz;
@@ -95,7 +95,7 @@ constexpr int kP2PTargets = 2;
 // base[g + G], ... of the n sources of a leaf; the lanes past n drop their last.
 // SELF: the sources are the targets' own leaf; target u skips source self[u].
 template <typename T, int G, bool SELF, bool BUF>
-__device__ inline void p2p_leaf(const typename Vec4<T>::type *__restrict__ base, int n, int g,
+__device__ __forceinline__ void p2p_leaf(const typename Vec4<T>::type *__restrict__ base, int n, int g,
                                 const T (&ox)[kP2PTargets], const T (&oy)[kP2PTargets], const T (&oz)[kP2PTargets],
                                 const int (&self)[kP2PTargets], double (&ph)[kP2PTargets], T (&fx)[kP2PTargets],
                                 T (&fy)[kP2PTargets], T (&fz)[kP2PTargets]) {
@@ -137,7 +137,7 @@ __device__ inline void p2p_leaf(const typename Vec4<T>::type *__restrict__ base,
 // 125 near-field leaves, G source groups per target; results stored by the
 // lanes of group 0.
 template <typename T, int G, bool BUF>
-__device__ inline void p2p_chunk(const typename Vec4<T>::type *__restrict__ X, const int32_t *__restrict__ pstart,
+__device__ __forceinline__ void p2p_chunk(const typename Vec4<T>::type *__restrict__ X, const int32_t *__restrict__ pstart,
                                  uint32_t cx, uint32_t cy, uint32_t cz, uint32_t nmask, int32_t s0, int32_t cnt,
                                  int32_t p0, int32_t pcnt, int32_t tb, T h, int lane, double *__restrict__ phi,
                                  T *__restrict__ field) {
@@ -162,7 +162,13 @@ __device__ inline void p2p_chunk(const typename Vec4<T>::type *__restrict__ X, c
     // an axis runs through -2h, -h, 0, h, 2h by adding h, and every one of
     // those sums is exact, so t - shift is rounded once, as t - d h is: the
     // innermost leaf costs an add and a subtract instead of three conversions
-    // and multiply-adds.
+    // and multiply-adds.  A leaf's range is read while the leaf before it in the
+    // row is summed.  FP32 rows are unrolled: at 10 to 30 sources a leaf is one to
+    // four turns of the source loop and what lies between leaves counts (3M-atom
+    // box, 11 atoms a leaf, 3.67 -> 3.44 ms; 1M, 30 a leaf, 2.12 -> 2.09; 125,001
+    // atoms 0.398 -> 0.371; 30,001, 7 a leaf, 0.111 -> 0.092; rolled 3.69 and 2.12
+    // ms).  FP64 rows are not, which would spill (3.92 -> 4.12 ms).
+    constexpr int kRow = sizeof(T) == 4 ? 2 * kWS + 1 : 1;
     T xs = -(T)kWS * h, ox[NT], oy[NT];
     for (int dx = -kWS; dx <= kWS; ++dx, xs += h) {
         T ys = -(T)kWS * h;
@@ -172,13 +178,22 @@ __device__ inline void p2p_chunk(const typename Vec4<T>::type *__restrict__ X, c
             T zs = -(T)kWS * h;
 #pragma unroll
             for (int u = 0; u < NT; ++u) oy[u] = ty[u] - ys;
+            auto leaf_at = [&](int dz) {
+                return morton3((cx + dx) & nmask, (cy + dy) & nmask, (cz + dz) & nmask);
+            };
+            uint32_t sc = leaf_at(-kWS);
+            int32_t j0 = pstart[sc], j1 = pstart[sc + 1];
+#pragma unroll kRow
             for (int dz = -kWS; dz <= kWS; ++dz, zs += h) {
-                if (dx == 0 && dy == 0 && dz == 0) continue;  // the own leaf: done above
-                const uint32_t sc = morton3((cx + dx) & nmask, (cy + dy) & nmask, (cz + dz) & nmask);
-                const int32_t j0 = pstart[sc];
+                sc = leaf_at(dz + 1);  // past the row's end: a leaf all the same, not taken
+                const int32_t n0 = pstart[sc], n1 = pstart[sc + 1];
+                if (dx != 0 || dy != 0 || dz != 0) {  // the own leaf: done above
 #pragma unroll
-                for (int u = 0; u < NT; ++u) oz[u] = tz[u] - zs;
-                p2p_leaf<T, G, false, BUF>(X + j0, pstart[sc + 1] - j0, g, ox, oy, oz, tl, ph, fx, fy, fz);
+                    for (int u = 0; u < NT; ++u) oz[u] = tz[u] - zs;
+                    p2p_leaf<T, G, false, BUF>(X + j0, j1 - j0, g, ox, oy, oz, tl, ph, fx, fy, fz);
+                }
+                j0 = n0;
+                j1 = n1;
             }
         }
     }
