@@ -13,7 +13,7 @@ the host cores.  Prints ONE JSON line.
 Other workloads (each one JSON line):
   --config C5 [--p P] [--prec fp64|mixed|bf16|split16]   3,000,008 atoms, levels 6
   --config C5 --sweep       p in (4, 8, 12, 16) x (fp64, mixed, bf16, split16), one line each
-  --config C4               32 charging windows (6k-48k atoms), one graph launch
+  --config C4               32 charging windows (6k-48k atoms), one call
                             of energies + forces and one of solute-solvent
                             energies per step, depths and P2P groups autotuned
                             (--autotune-cache FILE: taken from / stored in FILE)
@@ -52,10 +52,6 @@ def leaf_kernel(prec_name, info):
         return f"k_m2l_f16rows<false> x{info['m2l_launches']} (plain list, {info['m2l_entries']} entries)"
     t = {"fp64": "double", "split16": "PolF16x3F"}.get(prec_name, "float")
     return f"k_m2l_lds<{t}, false> x{info['m2l_launches']} ({kind} list, {info['m2l_entries']} entries)"
-
-
-def m2l_entries(prec_name, info):
-    return info["m2l_entries"]
 
 
 def m2l_flops(p, level, entries):
@@ -171,6 +167,68 @@ def sample_error(name, f, ph):
     return {"force_rms_rel": rel(fs, ref["force"]), "phi_rms_rel": rel(ps, ref["phi"]), "atoms": int(idx.size)}
 
 
+def roofline_lists(w, p, st, prec_name, info):
+    """The finest M2L level from the interaction lists (levels past the
+    convolution's, and the BF16 mode): algorithmic flops per level over its
+    event-timed duration on the plan's stream."""
+    entries = info["m2l_entries"]
+    flops_leaf = m2l_flops(p, w.levels, entries)
+    m2l_ms = st["m2l_leaf"]
+    achieved = flops_leaf / (m2l_ms * 1e-3) / 1e12
+    peak = PEAK_TFLOPS[prec_name]
+    kernel = leaf_kernel(prec_name, info)
+    # Three counts of the same launch's work: the folded list it executes
+    # (one K x K product per orbit of reflected offsets: achieved / frac), the
+    # dense 875-offset list it is equivalent to (O_st = D_s O_t D_s, the
+    # reflected operators differ by signs only), and what the matrix cores
+    # issue including the class padding of the rows and the column padding.
+    K = (p + 1) ** 2
+    dense = m2l_flops(p, w.levels, M2L_IL)
+    rows = info["m2l_rows"]
+    cols = 32 * ((K + 31) // 32) if prec_name in ("bf16", "split16") else info["Kp"]
+    # split operands: three FP16 products per operand pair
+    executed = flops_leaf * (rows * cols) / (K * K) * (3 if prec_name == "split16" else 1)
+    tflops = lambda f: f / (m2l_ms * 1e-3) / 1e12  # noqa: E731
+    return {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
+            "frac": round(achieved / peak, 4), "traffic": recorded_traffic(kernel, f"{w.name} levels {w.levels} p {p}"),
+            "kernel": f"{kernel} (M2L, level {w.levels})", "avg_ms": round(m2l_ms, 4),
+            "flops_per_level": flops_leaf,
+            "list_entries_per_cell": entries,
+            "flops_counts": {"folded": flops_leaf, "dense_875_equivalent": dense,
+                             "executed_with_padding": executed},
+            "frac_dense_equivalent": round(tflops(dense) / peak, 4),
+            "frac_executed_with_padding": round(tflops(executed) / peak, 4),
+            "folding": "profiles/m2l_folding.md"}
+
+
+# FP32 and FP64 peaks of the vector units (TFLOP/s)
+VECTOR_TFLOPS = {"fp64": 78.6}
+PAIR_FLOPS = 20  # 3 differences, r^2 (5), 1/r, q/r, q/r^3 (2), potential, field (6), to the leaf's total (1)
+
+
+def roofline_nearfield(F, plan, pos, w, st, prec_name):
+    """With the M2L as a convolution the near field is the longest kernel: its
+    source-target pairs over its event-timed duration, which it shares with the
+    far field's kernels on the other streams."""
+    import torch
+    _, _, start = F.fmm_bin(plan, pos)
+    n = 1 << w.levels
+    idx = torch.arange(n, device=pos.device)
+    spread = sum(((idx >> b) & 1) << (3 * b) for b in range(w.levels))
+    cell = (spread[:, None, None] << 2) | (spread[None, :, None] << 1) | spread[None, None, :]
+    cnt = (start[1:] - start[:-1]).long()[cell]
+    near = cnt
+    for ax in range(3):
+        near = sum(near.roll(d, ax) for d in range(-2, 3))
+    pairs = int((cnt * near).sum())
+    peak = VECTOR_TFLOPS.get(prec_name, 157.3)
+    achieved = pairs * PAIR_FLOPS / (st["p2p"] * 1e-3) / 1e12
+    return {"bound": "vector", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
+            "frac": round(achieved / peak, 4), "traffic": None, "kernel": "k_p2p (near field)",
+            "avg_ms": round(st["p2p"], 4), "pairs": pairs, "flops_per_pair": PAIR_FLOPS,
+            "m2l": f"convolution at levels 1..{w.levels}"}
+
+
 def run_single(args, w, p, prec_name, steps, warmup, fp64_leg, cpu_leg, graph_leg=False):
     import torch
     import paper_2003_13218_amd as F
@@ -210,38 +268,9 @@ def run_single(args, w, p, prec_name, steps, warmup, fp64_leg, cpu_leg, graph_le
     _, f, ph = F.fmm_energy_forces(plan, pos, q, forces=True, phi=True)
     err = sample_error(w.name, f, ph)
 
-    # dominant kernel: M2L at the finest level; algorithmic flops per launch
-    # divided by its event-timed average duration on the plan's stream
     info = F.fmm_plan_info(plan)
-    entries = m2l_entries(prec_name, info)
-    flops_leaf = m2l_flops(p, w.levels, entries)
-    m2l_ms = st["m2l_leaf"]
-    achieved = flops_leaf / (m2l_ms * 1e-3) / 1e12
-    peak = PEAK_TFLOPS[prec_name]
-    kernel = leaf_kernel(prec_name, info)
-    workload = f"{w.name} levels {w.levels} p {p}"
-    # Three counts of the same launch's work: the folded list it executes
-    # (one K x K product per orbit of reflected offsets: achieved / frac), the
-    # dense 875-offset list it is equivalent to (O_st = D_s O_t D_s, the
-    # reflected operators differ by signs only), and what the matrix cores
-    # issue including the class padding of the rows and the column padding.
-    K = (p + 1) ** 2
-    dense = m2l_flops(p, w.levels, M2L_IL)
-    rows = info["m2l_rows"]
-    cols = 32 * ((K + 31) // 32) if prec_name in ("bf16", "split16") else info["Kp"]
-    # split operands: three FP16 products per operand pair
-    executed = flops_leaf * (rows * cols) / (K * K) * (3 if prec_name == "split16" else 1)
-    tflops = lambda f: f / (m2l_ms * 1e-3) / 1e12  # noqa: E731
-    roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
-                "frac": round(achieved / peak, 4), "traffic": recorded_traffic(kernel, workload),
-                "kernel": f"{kernel} (M2L, level {w.levels})", "avg_ms": round(m2l_ms, 4),
-                "flops_per_level": flops_leaf,
-                "list_entries_per_cell": entries,
-                "flops_counts": {"folded": flops_leaf, "dense_875_equivalent": dense,
-                                 "executed_with_padding": executed},
-                "frac_dense_equivalent": round(tflops(dense) / peak, 4),
-                "frac_executed_with_padding": round(tflops(executed) / peak, 4),
-                "folding": "profiles/m2l_folding.md"}
+    roofline = (roofline_nearfield(F, plan, pos, w, st, prec_name) if info["m2l_conv_levels"] >= w.levels
+                else roofline_lists(w, p, st, prec_name, info))
     desc = {"C3": "333,333 waters + one -1 ion", "C5": "1,000,000 waters + 8 ions (net +3)"}.get(w.name, w.name)
     metric = ("atom-evals/s (energy+forces) at 1M atoms, mixed vs FP64 FMM, rel err <=1e-5" if w.name == "C3"
               else f"atom-evals/s (energy+forces) on {w.name} ({w.n} atoms)")
@@ -260,9 +289,8 @@ def run_single(args, w, p, prec_name, steps, warmup, fp64_leg, cpu_leg, graph_le
         "roofline": roofline,
     }
     if graph_leg:
-        # the same evaluation replayed as a captured HIP graph: a batch plan of
-        # this one box (fmm_energy_forces_batch captures on its first call and
-        # replays after; a graph branch keeps its near field on its own stream)
+        # the same evaluation as a batch of this one box, which keeps its near
+        # field on the box's own stream
         import numpy as np
         gplan = F.fmm_plan_batch([w.box], p, levels=[w.levels])
         F.fmm_plan_config(gplan, prec)
@@ -276,10 +304,10 @@ def run_single(args, w, p, prec_name, steps, warmup, fp64_leg, cpu_leg, graph_le
             eg, _ = F.fmm_energy_forces_batch(gplan, off, pos, q)
             gt.append(time.perf_counter() - t1)
         gmed = sorted(gt)[len(gt) // 2]
-        out["graph_replay"] = {"ms_per_call_median": round(1e3 * gmed, 4), "value": w.n / gmed,
+        out["batch_of_one"] = {"ms_per_call_median": round(1e3 * gmed, 4), "value": w.n / gmed,
                                "energy_rel_diff": abs(eg[0] - e_main) / abs(e_main)}
         F.fmm_destroy(gplan)
-        print(f"[bench] graph replay: {1e3 * gmed:.3f} ms/call", file=sys.stderr, flush=True)
+        print(f"[bench] batch of one: {1e3 * gmed:.3f} ms/call", file=sys.stderr, flush=True)
     if fp64_leg and prec_name != "fp64":
         n64 = max(3, steps // 4)
         dt64, e64, st64 = timed(F.FMM_FP64, n64, 1)
@@ -359,7 +387,7 @@ def run_batch(args):
     split[f"solute_solvent_{other}"] = round(1e3 * (time.perf_counter() - t1) / args.steps, 3)
     print(f"[bench] C4 split (ms/call): {split}", file=sys.stderr, flush=True)
     return {
-        "metric": "atom-evals/s (energy+forces+solute-solvent energy), 32 charging windows, one graph launch each",
+        "metric": "atom-evals/s (energy+forces+solute-solvent energy), 32 charging windows, one call each",
         "value": n * args.steps / dt, "unit": "atom-evals/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": 1e3 * dt / args.steps, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": DTYPES[args.prec],
@@ -388,7 +416,7 @@ def main():
                     help="C4: far-field scheme of the solute-solvent energy")
     ap.add_argument("--no-fp64", action="store_true", help="skip the FP64 comparison leg")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
-    ap.add_argument("--no-graph", action="store_true", help="skip the graph-replay leg")
+    ap.add_argument("--no-graph", action="store_true", help="skip the batch-of-one leg")
     ap.add_argument("--autotune-cache", default="",
                     help="C4: depths and P2P groups through this cache file (tuned and stored on a miss)")
     ap.add_argument("--cpu-reference", action="store_true",

@@ -923,8 +923,8 @@ static fmm_status far_field(fmm_plan_t pl, int64_t n, const void *xq, double *ph
     if (st != FMM_OK) return st;
     // Levels 1..lup (the upper tree: M2M, the level-0 lattice operator, M2L)
     // run on the second side stream once the M2M has produced level lup + 1,
-    // beside the M2L of the two finest levels on the plan stream (not inside a
-    // batch, whose boxes already run as parallel graph branches).  The upper
+    // beside the M2L of the finer levels on the plan stream (not inside a batch,
+    // whose boxes already run side by side).  The upper
     // tree's small launches wait behind the near field for CU slots; off the
     // plan stream they no longer hold back the finest levels.
     const int cl = conv_levels(pl);  // levels whose M2L is a convolution
@@ -1061,9 +1061,9 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
     // which leave most of the chip idle (measured on the 1M-atom box: forking
     // here saves 0.85 ms per step, forking after M2M none); the main stream
     // joins it before the corrections.  The moments of the corrections follow
-    // there, off the far field's chain.  Plans of a batch keep the near field on their own stream: a batch is already one
-    // parallel graph branch per box, and the nested fork inside a captured
-    // graph is not used (one such run ended in a host-side crash).
+    // there, off the far field's chain.  Plans of a batch keep the near field on
+    // their own stream: the boxes already run side by side, and the device has few
+    // hardware queues.
     const bool fork = !pl->in_batch;
     if (fork && !pl->side) return fail(pl, FMM_ERR_STATE, "plan has no side stream for the near field");
     hipStream_t ns = fork ? pl->side : s;
