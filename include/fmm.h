@@ -342,8 +342,9 @@ fmm_status fmm_lattice_tensor(fmm_plan_t plan, double *out, int64_t cap);
  *   fmm_solute_solvent_energy_batch and fmm_lambda_energy_batch.
  *
  * fmm_solute_solvent_energy_batch -- e_uv[w] (host out, nbox) of every box
- *   (see fmm_solute_solvent_energy) for mask (device, same rows as pos),
- *   one graph launch.  FMM_ERR_STATE without a preceding
+ *   (see fmm_solute_solvent_energy) for mask (device, same rows as pos): one
+ *   graph launch with FMM_UV_SPARSE, otherwise the boxes' second passes side by
+ *   side as in fmm_energy_forces_batch.  FMM_ERR_STATE without a preceding
  *   fmm_energy_forces_batch on this plan.
  *
  * fmm_autotune_batch -- times, on the given inputs, whole evaluations of
@@ -357,7 +358,7 @@ fmm_status fmm_lattice_tensor(fmm_plan_t plan, double *out, int64_t cap);
  *   P2P source-group count (p2p_groups[w]: 0, 1, 2, 4, 8 or 16), host nbox ints
  *   each; NULL keeps that setting.  Every value is checked before any box
  *   changes (FMM_ERR_INVALID).  Waits for the device; the next solute-solvent
- *   batch call captures its graph anew.
+ *   batch call with FMM_UV_SPARSE captures its graph anew.
  *
  * fmm_autotune_batch_cached -- fmm_autotune_batch with a cache file
  *   (cache_path: a text file, created if absent, one line per tuned batch).
@@ -380,7 +381,7 @@ fmm_status fmm_energy_forces_batch(fmm_plan_t plan, const int64_t *offsets, cons
                                    double *energies, double *forces);
 fmm_status fmm_solute_solvent_energy_batch(fmm_plan_t plan, const uint8_t *mask, double *e_uv);
 /* Batched fmm_lambda_energy: lambdas (host, nbox) in, v_lambda and dv_dlambda
- * (host, nbox; either may be NULL) out, one graph launch. */
+ * (host, nbox; either may be NULL) out; runs as fmm_solute_solvent_energy_batch. */
 fmm_status fmm_lambda_energy_batch(fmm_plan_t plan, const uint8_t *mask, const double *lambdas, double *v_lambda,
                                    double *dv_dlambda);
 fmm_status fmm_autotune_batch(fmm_plan_t plan, const int64_t *offsets, const double *pos, const double *q,

@@ -155,7 +155,7 @@ struct fmm_plan {
     bool in_batch = false;  // sub-plan of a batch plan
 
     // batch plans (fmm_plan_batch): one sub-plan per box, run on parallel
-    // streams (the solute-solvent pass as one captured HIP graph)
+    // streams (the one-sided solute-solvent pass as one captured HIP graph)
     bool is_batch = false;
     std::vector<fmm_plan_t> sub;
     std::vector<int64_t> sub_natoms;  // atom counts the levels were chosen for
@@ -1842,20 +1842,20 @@ static fmm_status batch_inputs(fmm_plan_t pl) {
     return FMM_OK;
 }
 
-// The solute-solvent pass as one graph, captured for a new key and replayed for
-// the same one: every box's branch (branches true), then tail's work on the
-// batch stream.  The caller synchronises.
-template <typename F, typename G>
-static fmm_status batch_run(fmm_plan_t pl, fmm_plan::Graph &g, const std::vector<int64_t> &key, const int64_t *off,
-                            F enqueue, bool branches, G tail) {
+// work(): launches on the batch stream, captured as one graph for a new key and
+// replayed for the same one.  Their kernel arguments may point to what lives as
+// long as the graph only (the uploaded tables and the operators; a changed table
+// address drops it): a box's workspace moves when a larger box comes by, so every
+// kernel that takes it directly is launched each time.  The caller synchronises.
+template <typename F>
+static fmm_status batch_graph(fmm_plan_t pl, fmm_plan::Graph &g, const std::vector<int64_t> &key, F work) {
     hipStream_t cs = pl->stream;
     if (!g.exec || g.key != key) {
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
         g.exec = nullptr;
         g.key.clear();
         HIPCHK(pl, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "graph capture");
-        fmm_status st = branches ? batch_branches(pl, off, enqueue) : FMM_OK;
-        if (st == FMM_OK) st = tail();
+        const fmm_status st = work();
         hipGraph_t graph = nullptr;
         const hipError_t ec = hipStreamEndCapture(cs, &graph);
         if (st != FMM_OK) {
@@ -1873,8 +1873,6 @@ static fmm_status batch_run(fmm_plan_t pl, fmm_plan::Graph &g, const std::vector
         g.exec = exec;
         g.key = key;
     }
-    const fmm_status st = batch_inputs(pl);
-    if (st != FMM_OK) return st;
     HIPCHK(pl, hipGraphLaunch(g.exec, cs), "graph launch");
     return FMM_OK;
 }
@@ -1972,7 +1970,7 @@ static fmm_status solute_solvent_batch(fmm_plan_t pl, const uint8_t *mask, const
     key.push_back(soft ? 1 : 0);
     for (fmm_plan_t b : pl->sub) b->uv_d0 = b->uv_dsc = b->uv_dl = 0.0;
     // every box's stages in one launch per stage; the symmetric scheme first
-    // runs each box's dense second pass as a parallel branch
+    // runs each box's dense second pass on the box's stream
     const bool sparse = (pl->uv_scheme & FMM_UV_SPARSE) != 0;
     UvTables t;
     for (size_t w = 0; w < nb; ++w) {
@@ -1991,22 +1989,26 @@ static fmm_status solute_solvent_batch(fmm_plan_t pl, const uint8_t *mask, const
         pl->g_uv.key.clear();
     }
     const bool fp64 = pl->prec == FMM_FP64;
-    st = batch_run(
-        pl, pl->g_uv, key, off,
-        [&](size_t w) -> fmm_status {
+    auto stages = [&]() -> fmm_status {
+        const fmm_status s2 = fp64 ? enqueue_uv_stages<double>(pl, t, sparse, *pl->op, pl->stream)
+                                   : enqueue_uv_stages<float>(pl, t, sparse, *pl->op, pl->stream);
+        if (s2 != FMM_OK) return s2;
+        HIPCHK(pl, hipMemcpyAsync(pl->h_uvsc, pl->uvsc.ptr, sizeof(double) * kScalars * nb, hipMemcpyDeviceToHost,
+                                  pl->stream),
+               "readback");
+        return FMM_OK;
+    };
+    if ((st = batch_inputs(pl)) != FMM_OK) return st;
+    if (sparse) {
+        st = batch_graph(pl, pl->g_uv, key, stages);
+    } else {
+        st = batch_branches(pl, off, [&](size_t w) -> fmm_status {
             fmm_plan_t b = pl->sub[w];
             return fp64 ? enqueue_uv_dense<double>(b, mask + off[w]) : enqueue_uv_dense<float>(b, mask + off[w]);
-        },
-        !sparse,
-        [&]() -> fmm_status {
-            const fmm_status s2 = fp64 ? enqueue_uv_stages<double>(pl, t, sparse, *pl->op, pl->stream)
-                                       : enqueue_uv_stages<float>(pl, t, sparse, *pl->op, pl->stream);
-            if (s2 != FMM_OK) return s2;
-            HIPCHK(pl, hipMemcpyAsync(pl->h_uvsc, pl->uvsc.ptr, sizeof(double) * kScalars * nb, hipMemcpyDeviceToHost,
-                                      pl->stream),
-                   "readback");
-            return FMM_OK;
         });
+        if (st == FMM_OK) st = stages();
+        if (st != FMM_OK) (void)hipDeviceSynchronize();  // boxes already enqueued read the caller's mask
+    }
     if (st != FMM_OK) return st;
     HIPCHK(pl, hipStreamSynchronize(pl->stream), "synchronize");
     for (size_t w = 0; w < nb; ++w) {

@@ -1,0 +1,174 @@
+// The host side of the library (plans, workspaces, batches) on a stand-in for the
+// HIP runtime: this program defines the runtime's functions itself, so the calls of
+// libfmm.so land here.  Device memory is an address range without storage, kernels
+// are counted and not run, results are zeros.  What is checked is which calls are
+// made and what they return.  Usage: plan_check CASE; prints "ok" or what is wrong.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "fmm.h"
+
+static struct Fake {
+    size_t total = (size_t)288 << 30, used = 0;  // bytes of the device
+    uintptr_t next = (uintptr_t)1 << 44;
+    std::map<uintptr_t, size_t> live;
+    long launched = 0, captured = 0, graphs = 0;
+    bool capturing = false;
+    dim3 grid, block;
+    size_t shared = 0;
+    hipStream_t stream = nullptr;
+} fk;
+
+extern "C" {
+hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipDeviceTotalMem(size_t *b, hipDevice_t) { *b = fk.total; return hipSuccess; }
+hipError_t hipMemGetInfo(size_t *f, size_t *t) { *f = fk.total - fk.used; *t = fk.total; return hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) {
+    std::memset(p, 0, sizeof *p);
+    std::strcpy(p->gcnArchName, "gfx950");
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t b) {
+    *p = nullptr;
+    if (fk.capturing) return hipErrorStreamCaptureUnsupported;
+    if (b > fk.total - fk.used) return hipErrorOutOfMemory;
+    fk.used += b;
+    fk.live[fk.next] = b;
+    *p = (void *)fk.next;
+    fk.next += (b + 4095) / 4096 * 4096 + 4096;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    auto it = fk.live.find((uintptr_t)p);
+    if (it == fk.live.end()) {
+        std::printf("free of %p, which is not allocated\n", p);
+        std::exit(1);
+    }
+    fk.used -= it->second;
+    fk.live.erase(it);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t b, unsigned) { *p = std::calloc(1, b); return hipSuccess; }
+hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
+static hipError_t copy(void *d, const void *s, size_t b, hipMemcpyKind k) {
+    auto inside = [&](const void *p) {  // of one live allocation
+        auto it = fk.live.upper_bound((uintptr_t)p);
+        return it != fk.live.begin() && (--it, (uintptr_t)p + b <= it->first + it->second);
+    };
+    if ((k != hipMemcpyDeviceToHost && !inside(d)) || (k != hipMemcpyHostToDevice && !inside(s))) {
+        std::printf("copy of %zu bytes outside the allocations\n", b);
+        std::exit(1);
+    }
+    if (k == hipMemcpyDeviceToHost) std::memset(d, 0, b);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void *d, const void *s, size_t b, hipMemcpyKind k) { return copy(d, s, b, k); }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t b, hipMemcpyKind k, hipStream_t) { return copy(d, s, b, k); }
+hipError_t hipMemcpyToSymbol(const void *, const void *, size_t, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) { *p = (void *)((uintptr_t)1 << 43); return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)std::malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { fk.capturing = true; return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) {
+    fk.capturing = false;
+    *g = (hipGraph_t)std::malloc(1);
+    return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t g) { std::free(g); return hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t, hipGraphNode_t *, char *, size_t) {
+    *e = (hipGraphExec_t)std::malloc(1);
+    return hipSuccess;
+}
+hipError_t hipGraphExecDestroy(hipGraphExec_t e) { std::free(e); return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { ++fk.graphs; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, hipStream_t s) {
+    fk.grid = g;
+    fk.block = b;
+    fk.shared = sh;
+    fk.stream = s;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, hipStream_t *s) {
+    *g = fk.grid;
+    *b = fk.block;
+    *sh = fk.shared;
+    *s = fk.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *, dim3 g, dim3 b, void **, size_t, hipStream_t) {
+    if (g.x == 0 || g.y == 0 || g.z == 0 || b.x * b.y * b.z == 0 || b.x * b.y * b.z > 1024) {
+        std::printf("launch of %u x %u x %u blocks of %u threads\n", g.x, g.y, g.z, b.x * b.y * b.z);
+        std::exit(1);
+    }
+    ++(fk.capturing ? fk.captured : fk.launched);
+    return hipSuccess;
+}
+}
+
+static int bad = 0;
+#define CHECK(c)                                                      \
+    do {                                                              \
+        if (!(c)) {                                                   \
+            std::printf("line %d: %s\n", __LINE__, #c);               \
+            ++bad;                                                    \
+        }                                                             \
+    } while (0)
+
+static double *device(size_t n) {  // an input or output array
+    void *p = nullptr;
+    if (hipMalloc(&p, sizeof(double) * n) != hipSuccess) std::abort();
+    return (double *)p;
+}
+
+// The symmetric solute-solvent pass takes the boxes' workspaces as kernel arguments,
+// and these move when a larger box comes by: its kernels are launched on every call.
+static void batch_replay() {
+    const double box[3] = {20.0, 21.0, 22.0};
+    const int levels[3] = {2, 3, 1};
+    const int64_t a[4] = {0, 300, 700, 900}, b[4] = {0, 3000, 7000, 9000};
+    double *pos = device(3 * 9000), *q = device(9000), e[3], u[3];
+    const uint8_t *mask = (const uint8_t *)device(9000 / 8);
+    fmm_plan_t plan = nullptr;
+    CHECK(fmm_plan_batch(3, box, nullptr, levels, 4, &plan) == FMM_OK);
+    for (int scheme : {(int)FMM_UV_SYMMETRIC, FMM_UV_SYMMETRIC | FMM_UV_SWAP}) {
+        CHECK(fmm_plan_options(plan, FMM_BOUNDARY_CONDUCTING, scheme) == FMM_OK);
+        CHECK(fmm_energy_forces_batch(plan, a, pos, q, e, nullptr) == FMM_OK);
+        CHECK(fmm_solute_solvent_energy_batch(plan, mask, u) == FMM_OK);
+        CHECK(fmm_energy_forces_batch(plan, b, pos, q, e, nullptr) == FMM_OK);
+        CHECK(fmm_energy_forces_batch(plan, a, pos, q, e, nullptr) == FMM_OK);
+        const long before = fk.launched;
+        CHECK(fmm_solute_solvent_energy_batch(plan, mask, u) == FMM_OK);
+        CHECK(fk.launched - before >= 3 * 8);
+    }
+    fmm_destroy(plan);
+}
+
+int main(int argc, char **argv) {
+    const std::string c = argc > 1 ? argv[1] : "";
+    if (c == "batch_replay") batch_replay();
+    else {
+        std::printf("no such case\n");
+        return 2;
+    }
+    if (!bad) std::printf("ok\n");
+    return bad != 0;
+}
