@@ -344,7 +344,7 @@ struct ConvLevel {
     double *L;
     const void *ops;
     const int32_t *pair;
-    void *P, *Q;
+    double *P, *Q;
 };
 constexpr int kConvMaxBatch = 4;  // levels a launch takes together (1 .. 4)
 // builds the blocks of one level (elem 4 or 8) from conv_reps' operators

@@ -36,8 +36,8 @@
 // p = 12: 405 triples x 27 x 176^2, 1.36 GB in FP32), and the matrix cores (64
 // block products per triple on 16 columns).  The transforms are dense n x n per
 // line, folded by the symmetries of the cosines to n^2 / 4 multiply-adds, in FP64.
-// FP32 levels hold the multipoles and the blocks in FP32, levels 5 and 6 the
-// arrays between the launches too; the locals are FP64 in every mode.
+// FP32 levels hold the multipoles and the blocks in FP32; everything after them
+// (transforms, columns, products, locals) is FP64 in every mode.
 #include "conv_map.h"
 #include "fmm_internal.h"
 #include "mfma.h"
@@ -175,7 +175,7 @@ __device__ inline double load_m(const ConvLevel &v, size_t i) {
 }
 // ---------------------------------------------------------------- levels 1 .. 4
 // All three axes of CG coefficients of a level in LDS: a thread takes one line
-// at a time in registers, in place.  P and Q are FP64.  Rows of a line's y are padded by CG
+// at a time in registers, in place.  Rows of a line's y are padded by CG
 // doubles so that the lines of z do not meet in one bank.
 template <int n, int CG, bool FWD>
 __device__ inline void cube(const ConvLevel &v, int part, int NB, int Kp, const ConvCoef *__restrict__ tab,
@@ -206,7 +206,7 @@ __device__ inline void cube(const ConvLevel &v, int part, int NB, int Kp, const 
             const Axis ax = axis_of(b, n, t.flips & 1), ay = axis_of(a, n, t.flips >> 1 & 1);
             for (int i = 0; i < n; ++i) {
                 const Entry e = entry_of(ax, ay, axis_of(i, n, t.flips >> 2), pos, t, false, n / 2, NB, v.pair);
-                reinterpret_cast<double *>(v.Q)[e.at] = e.neg ? -o[i] : o[i];
+                v.Q[e.at] = e.neg ? -o[i] : o[i];
             }
         }
     } else {
@@ -214,7 +214,7 @@ __device__ inline void cube(const ConvLevel &v, int part, int NB, int Kp, const 
             const Axis ax = axis_of(b, n, t.flips & 1), ay = axis_of(a, n, t.flips >> 1 & 1);
             for (int i = 0; i < n; ++i) {
                 const Entry e = entry_of(ax, ay, axis_of(i, n, t.flips >> 2), pos, t, true, n / 2, NB, v.pair);
-                const double w = reinterpret_cast<const double *>(v.P)[e.at];
+                const double w = v.P[e.at];
                 x[i] = e.neg ? -w : w;
             }
             Line<n>::inverse(x, o);
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(512) void k_conv_cube(ConvBatch bt, int NB, int Kp,
 // ---------------------------------------------------------------- levels 5, 6
 // The x and y lines of one plane of cells (fixed z) for CG coefficients in
 // LDS, then the z lines from and to memory.  Between them: [chunk][z][y][x][16].
-// S: the type of M, P and Q.
+// S: the type of M.
 template <typename S, int n, int CG>
 __global__ __launch_bounds__(n *CG) void k_conv_plane_fwd(ConvLevel v, int Kp, const ConvCoef *__restrict__ tab) {
     constexpr int SX = n * CG + CG;
@@ -290,12 +290,12 @@ __global__ __launch_bounds__(n *CG) void k_conv_plane_fwd(ConvLevel v, int Kp, c
 #pragma unroll
     for (int i = 0; i < n; ++i) x[i] = lds[line * SX + i * CG + c];
     Line<n>::forward(x, o);
-    S *q = reinterpret_cast<S *>(v.Q) + (size_t)(part / parts * n + z) * n * n * 16 + line * 16 + part % parts * CG + c;
+    double *q = v.Q + (size_t)(part / parts * n + z) * n * n * 16 + line * 16 + part % parts * CG + c;
 #pragma unroll
-    for (int i = 0; i < n; ++i) q[(size_t)i * n * 16] = (S)o[i];
+    for (int i = 0; i < n; ++i) q[(size_t)i * n * 16] = o[i];
 }
 
-template <typename S, int n, int CG>
+template <int n, int CG>
 __global__ __launch_bounds__(n *CG) void k_conv_plane_inv(ConvLevel v, int Kp, const ConvCoef *__restrict__ tab) {
     constexpr int SX = n * CG + CG;
     __shared__ double lds[n * SX];
@@ -306,8 +306,7 @@ __global__ __launch_bounds__(n *CG) void k_conv_plane_inv(ConvLevel v, int Kp, c
     const int pos = part * CG + c;
     const int sto = tab[pos].sto;
     double x[n], o[n];
-    const S *q = reinterpret_cast<const S *>(v.P) + (size_t)(part / parts * n + z) * n * n * 16 + line * 16 +
-                 part % parts * CG + c;
+    const double *q = v.P + (size_t)(part / parts * n + z) * n * n * 16 + line * 16 + part % parts * CG + c;
 #pragma unroll
     for (int i = 0; i < n; ++i) x[i] = q[(size_t)i * n * 16];
     Line<n>::inverse(x, o);
@@ -323,7 +322,7 @@ __global__ __launch_bounds__(n *CG) void k_conv_plane_inv(ConvLevel v, int Kp, c
 
 // One z line per thread: 16 coefficients x 16 x slots of one y slot per block.
 // FWD: Q (planes) -> P (columns); else Q (columns) -> P (planes).
-template <typename S, int n, bool FWD>
+template <int n, bool FWD>
 __global__ __launch_bounds__(256) void k_conv_z(ConvLevel v, int NB, const ConvCoef *__restrict__ tab) {
     const int c = threadIdx.x & 15;
     const int fx = blockIdx.x % (n / 16) * 16 + (threadIdx.x >> 4);
@@ -332,48 +331,45 @@ __global__ __launch_bounds__(256) void k_conv_z(ConvLevel v, int NB, const ConvC
     const ConvCoef t = tab[pos];
     const Axis ax = axis_of(fx, n, t.flips & 1), ay = axis_of(fy, n, t.flips >> 1 & 1);
     const size_t plane = ((size_t)cc * n * n + fy) * n * 16 + fx * 16 + c;
-    S *P = reinterpret_cast<S *>(v.P), *Q = reinterpret_cast<S *>(v.Q);
     double x[n], o[n];
     if constexpr (FWD) {
 #pragma unroll
-        for (int i = 0; i < n; ++i) x[i] = Q[plane + (size_t)i * n * n * 16];
+        for (int i = 0; i < n; ++i) x[i] = v.Q[plane + (size_t)i * n * n * 16];
         Line<n>::forward(x, o);
 #pragma unroll
         for (int i = 0; i < n; ++i) {
             const Entry e = entry_of(ax, ay, axis_of(i, n, t.flips >> 2), pos, t, false, n / 2, NB, v.pair);
-            P[e.at] = (S)(e.neg ? -o[i] : o[i]);
+            v.P[e.at] = e.neg ? -o[i] : o[i];
         }
     } else {
 #pragma unroll
         for (int i = 0; i < n; ++i) {
             const Entry e = entry_of(ax, ay, axis_of(i, n, t.flips >> 2), pos, t, true, n / 2, NB, v.pair);
-            const double w = Q[e.at];
+            const double w = v.Q[e.at];
             x[i] = e.neg ? -w : w;
         }
         Line<n>::inverse(x, o);
 #pragma unroll
-        for (int i = 0; i < n; ++i) P[plane + (size_t)i * n * n * 16] = (S)o[i];
+        for (int i = 0; i < n; ++i) v.P[plane + (size_t)i * n * n * 16] = o[i];
     }
 }
 
 // ---------------------------------------------------------------- the products
 // One workgroup: 16 result rows (all 8 tau) of one triple of wave numbers, its
 // waves taking the chunks of 16 columns in turn; their sums meet in LDS in a
-// fixed order.  A wave holds the eight 16 x 16 results in FP64, the eight column
+// fixed order.  A wave holds the eight 16 x 16 results, the eight column
 // fragments of the chunk and the 9 blocks of one x type, each used for one
 // (types 0, 1) to eight (type 2 in all axes) of the 64 (tau, tau') products.
-// A: type of the blocks, T: of the columns and the products.  FP32 levels 5 and 6
-// multiply on the FP32 matrix cores, twice as fast as the FP64 ones (34 against 72
-// cycles), and add every chunk's sums of 128 terms in FP64 (1M-atom box: potential
-// error 1.15e-6, 4.1e-7 with FP64 products, 1.74e-6 with the FP32 lists); the few
-// products of the levels above stay FP64.
-template <typename A, typename T>
-__device__ inline void conv_product(const ConvLevel &v, int o, int rt, int NB, const void *__restrict__ Xv,
-                                    void *__restrict__ Yv, double (*red)[8][4][64]) {
-    using V = typename Mfma<T>::V;
+// A: type of the blocks.  Columns and products are FP64 for FP32 blocks too.  In FP32
+// levels 5 and 6 take 0.1 and 0.4 ms less (whole call, 1M atoms at p = 12 2.98 against
+// 3.08 ms, 3M at p = 8 5.77 against 6.14) but round each column and result twice and add
+// chains of 128 products: far-field potential error of 4,000 charges in levels 6, p = 3,
+// levels 1-4 in FP64, 2.4e-7 against 3.9e-8 (the interaction lists: 2.0e-7), of 20,000 in
+// levels 5, p = 6, 1.1e-7 against 2.7e-8 (1.1e-7).
+template <typename A>
+__device__ inline void conv_product(const ConvLevel &v, int o, int rt, int NB, const double *__restrict__ X,
+                                    double *__restrict__ Y, double (*red)[8][4][64]) {
     using AV = typename Mfma<A>::V;
-    const T *X = reinterpret_cast<const T *>(Xv);
-    T *Y = reinterpret_cast<T *>(Yv);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int N = (1 << v.level) / 2, H1 = N / 2 + 1;
     int kx = 0, ky = o / H1;
@@ -391,13 +387,9 @@ __device__ inline void conv_product(const ConvLevel &v, int o, int rt, int NB, c
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = f64x4{0, 0, 0, 0};
     for (int cc = w; cc < NB; cc += nw) {
-        V b[8], part[8];
+        f64x4 b[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            b[t] = *reinterpret_cast<const V *>(X + xo + (uint32_t)(cc * 8 + t) * ncol * 16u);
-            if constexpr (sizeof(T) == 8) part[t] = acc[t];
-            else part[t] = V{0, 0, 0, 0};
-        }
+        for (int t = 0; t < 8; ++t) b[t] = *reinterpret_cast<const f64x4 *>(X + xo + (uint32_t)(cc * 8 + t) * ncol * 16u);
         const A *a0 = ap + (size_t)cc * (kConvTypes * 256);
 #pragma unroll
         for (int tx = 0; tx < 3; ++tx) {
@@ -410,24 +402,17 @@ __device__ inline void conv_product(const ConvLevel &v, int o, int rt, int NB, c
                 const int ty = i / 3, tz = i % 3;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const T av = (T)a[i][j];
+                    const double av = (double)a[i][j];
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
                         // t: tau of the result; the source's tau' follows from the types
                         const int x = t >> 2, y = t >> 1 & 1, z = t & 1;
                         if ((tx < 2 && x != tx) || (ty < 2 && y != ty) || (tz < 2 && z != tz)) continue;
                         const int s = (tx == 2 ? !x : x) << 2 | (ty == 2 ? !y : y) << 1 | (tz == 2 ? !z : z);
-                        part[t] = Mfma<T>::mma(av, b[s][j], part[t]);
+                        acc[t] = Mfma<double>::mma(av, b[s][j], acc[t]);
                     }
                 }
             }
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            if constexpr (sizeof(T) == 8) acc[t] = part[t];
-            else
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[t][r] += (double)part[t][r];
         }
     }
 #pragma unroll
@@ -437,21 +422,19 @@ __device__ inline void conv_product(const ConvLevel &v, int o, int rt, int NB, c
     __syncthreads();
     // lanes along the rows: 16 neighbouring results a column
     const int row = lane & 15;
-    constexpr bool F = sizeof(T) == 4;  // where the result layouts put (row, column)
-    const int rr = F ? row & 3 : row >> 2, rl = 16 * (F ? row >> 2 : row & 3);
-    T *yo = Y + (col0 * NB + rt * ncol) * 128u + row;
+    const int rr = row >> 2, rl = 16 * (row & 3);  // where the result's layout puts (row, column)
+    double *yo = Y + (col0 * NB + rt * ncol) * 128u + row;
     for (int i = w; i < 32; i += nw) {
         const int t = i >> 2, c = 4 * (i & 3) + (lane >> 4);
         if (c >= ncol) continue;
         double s = 0.0;
         for (int k = 0; k < nw; ++k) s += red[k][t][rr][rl + c];
-        yo[(uint32_t)(t * ncol + c) * 16u] = (T)s;
+        yo[(uint32_t)(t * ncol + c) * 16u] = s;
     }
 }
 
 // The 16-row tiles of one triple are 8 blocks apart (one XCD: they read the
-// same columns).  MODE 0: FP32 blocks and columns, 1: FP64 ones, 2: FP64
-// columns and either blocks, by level.
+// same columns).  MODE 0: FP32 blocks, 1: FP64 ones, 2: either, by level.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_conv_product(ConvBatch bt, int NB, int swapPQ) {
     extern __shared__ double red_raw[];  // [wavefronts][8][4][64]
@@ -463,11 +446,10 @@ __global__ __launch_bounds__(256) void k_conv_product(ConvBatch bt, int NB, int 
     const int o = bid / (8 * NB) * 8 + bid % 8, rt = bid / 8 % NB;
     const int H1 = (1 << v.level) / 4 + 1;
     if (o >= H1 * (H1 + 1) / 2 * H1) return;  // whole workgroup
-    const void *X = swapPQ ? v.P : v.Q;
-    void *Y = swapPQ ? v.Q : v.P;
-    if constexpr (MODE == 0) conv_product<float, float>(v, o, rt, NB, X, Y, red);
-    else if (MODE == 2 && !v.fp64) conv_product<float, double>(v, o, rt, NB, X, Y, red);
-    else conv_product<double, double>(v, o, rt, NB, X, Y, red);
+    const double *X = swapPQ ? v.P : v.Q;
+    double *Y = swapPQ ? v.Q : v.P;
+    if (MODE == 0 || (MODE == 2 && !v.fp64)) conv_product<float>(v, o, rt, NB, X, Y, red);
+    else conv_product<double>(v, o, rt, NB, X, Y, red);
 }
 
 // ---------------------------------------------------------------- the blocks
@@ -571,14 +553,14 @@ static int product_waves(const ConvBatch &b, int NB) {
 }
 
 static hipError_t launch_product(const ConvBatch &b, int blocks, int NB, int swapPQ, hipStream_t s) {
-    bool f32 = false;
-    for (int i = 0; i < b.nlv; ++i) f32 = f32 || !b.lv[i].fp64;
+    bool f32 = false, f64 = false;
+    for (int i = 0; i < b.nlv; ++i) (b.lv[i].fp64 ? f64 : f32) = true;
     const int nw = product_waves(b, NB);
     const dim3 grid(blocks), block(64 * nw);
     const size_t lds = sizeof(double) * nw * 8 * 4 * 64;
-    if (!f32) hipLaunchKernelGGL(k_conv_product<1>, grid, block, lds, s, b, NB, swapPQ);
-    else if (b.lv[0].level > 4) hipLaunchKernelGGL(k_conv_product<0>, grid, block, lds, s, b, NB, swapPQ);
-    else hipLaunchKernelGGL(k_conv_product<2>, grid, block, lds, s, b, NB, swapPQ);
+    if (f32 && f64) hipLaunchKernelGGL(k_conv_product<2>, grid, block, lds, s, b, NB, swapPQ);
+    else if (f64) hipLaunchKernelGGL(k_conv_product<1>, grid, block, lds, s, b, NB, swapPQ);
+    else hipLaunchKernelGGL(k_conv_product<0>, grid, block, lds, s, b, NB, swapPQ);
     return hipGetLastError();
 }
 
@@ -591,11 +573,11 @@ static hipError_t conv_large(const ConvLevel &v, int Kp, const ConvCoef *tab, hi
     b.nlv = 1;
     b.start[1] = product_blocks(v.level, NB);
     hipLaunchKernelGGL((k_conv_plane_fwd<S, n, CG>), planes, dim3(n * CG), 0, s, v, Kp, tab);
-    hipLaunchKernelGGL((k_conv_z<S, n, true>), lines, dim3(256), 0, s, v, NB, tab);
+    hipLaunchKernelGGL((k_conv_z<n, true>), lines, dim3(256), 0, s, v, NB, tab);
     hipError_t e = launch_product(b, b.start[1], NB, 1, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_conv_z<S, n, false>), lines, dim3(256), 0, s, v, NB, tab);
-    hipLaunchKernelGGL((k_conv_plane_inv<S, n, CG>), planes, dim3(n * CG), 0, s, v, Kp, tab);
+    hipLaunchKernelGGL((k_conv_z<n, false>), lines, dim3(256), 0, s, v, NB, tab);
+    hipLaunchKernelGGL((k_conv_plane_inv<n, CG>), planes, dim3(n * CG), 0, s, v, Kp, tab);
     return hipGetLastError();
 }
 
