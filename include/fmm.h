@@ -67,7 +67,9 @@ typedef enum {
      * multipoles summed in FP64; levels 0-3, the M2L's sums and the locals of
      * every level that takes it as a convolution, the lattice operator, the
      * charged-system, quadrupole and dipole terms and the energy reduction
-     * in FP64 */
+     * in FP64.  The charges of the near field and the tree are rounded to FP32;
+     * the energy is that of the exact ones to first order (so it differs from
+     * 1/2 sum q phi by the rounding of q), phi and forces are not corrected */
     FMM_MIXED = 1,
     /* as FMM_MIXED, but the FP32 levels' M2L takes BF16 operands (operators
      * and multipoles rounded to bfloat16, 8 significant bits) with FP32

@@ -144,13 +144,18 @@ __global__ __launch_bounds__(kRedBlock) void k_finalize(
     // under the vacuum boundary (mu_w = 0) the dipole surface term
     // (2 pi / 3V) mu.mu cancels the -mu.mu of the quadrupole/dipole terms
     const double wx = mu_w * mux, wy = mu_w * muy, wz = mu_w * muz;
+    // The potentials are those of the charges the tree and the near field hold,
+    // rounded to T: q' = q + d.  The energy is quadratic in the charges, so
+    // 1/2 sum (2 q - q') phi' is that of q up to d^2, where 1/2 sum q phi' would miss
+    // it by d (water's two charges are both 2e-8 low in FP32: 3M atoms, -2e-8).
+    auto weight = [](double exact, double held) { return 2.0 * exact - held; };
     NSum e[1];
     for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n;
          s += (int64_t)gridDim.x * blockDim.x) {
         const int64_t i = perm[s];
         const double qi = xs[4 * s + 3];
         const double ph = phi_nf[s] + phi_ff[s];
-        e[0].add(0.5 * qi * ph);  // E_pair; the t00 part is added once below
+        e[0].add(0.5 * weight(qi, (double)(T)qi) * ph);  // E_pair; the t00 part is added once below
         const double x = xs[4 * s], y = xs[4 * s + 1], z = xs[4 * s + 2];
         if (phi_out)
             phi_out[i] = ph + c_bg + c23 * (S + Q * (x * x + y * y + z * z) - 2.0 * (wx * x + wy * y + wz * z));
@@ -178,7 +183,7 @@ __global__ __launch_bounds__(kRedBlock) void k_finalize(
         NSum t;
         t.merge(v[0].s, v[0].c);
         t.add(-M_PI * Q * Q / (2.0 * V * kappa * kappa));
-        t.add(0.5 * t00b * Q * m0[0]);
+        t.add(0.5 * t00b * (sizeof(T) == 8 ? Q : weight(Q, m0[0])) * m0[0]);
         t.add(2.0 * M_PI / (3.0 * V) * (Q * S - mu_w * mu2));
         host[8] = t.value();
         host[9] = v[0].value();

@@ -28,3 +28,22 @@ def test_far_field_of_deep_levels(fmm, n, box, levels, p):
     err = float((got - ref).norm() / ref.norm())
     print(f"{n} atoms, levels {levels}, p {p}: far-field potential {err:.2e}")
     assert err < 1e-7
+
+
+@pytest.mark.parametrize("net", [0.0, 3.0])
+@pytest.mark.parametrize("levels", [2, 5])
+def test_energy_of_charges_between_fp32_numbers(fmm, levels, net):
+    # charges s (1 + d), d = 2^-25, are s in FP32; the energy of the exact ones is
+    # (1 + d)^2 that of s, where FP32 potentials alone would give 1 + d
+    n, box, d = 2000, 20.0, 2.0 ** -25
+    pos, _ = workloads.random_charges(n, box, seed=11, net=0.0)
+    s = np.where(np.arange(n) % 2 == 0, 1.0, -1.0)
+    s[0] += net
+    assert np.all((s * (1 + d)).astype(np.float32) == s)
+    plan = fmm.fmm_plan(box, levels, 6)
+    fmm.fmm_plan_config(plan, fmm.FMM_MIXED)
+    e1, _, phi = fmm.fmm_energy_forces(plan, _t(pos), _t(s), phi=True)
+    e2, _, _ = fmm.fmm_energy_forces(plan, _t(pos), _t(s * (1 + d)))
+    scale = 0.5 * float(np.abs(s) @ np.abs(phi.cpu().numpy()))
+    # 2,000 FP64 terms of that total size, rounded once each, and d^2
+    assert abs(e2 - e1 * (1 + 2 * d)) < 1e-13 * scale, (e2 / e1 - 1) / d
