@@ -106,7 +106,10 @@ typedef enum {
  * about 0.42 8^levels K^2 elements of the level's type (27 Kp^2 per triple of
  * wave numbers; 1,000,000 atoms, levels 5, p 12: 1.4 GB in FP32, 2.7 GB in
  * FP64).  A level whose operators would take more than 64 GiB or a quarter of
- * the device's memory, or find no memory, takes the interaction lists.
+ * the device's memory, or find no memory, takes the interaction lists.  The
+ * operators of FMM_FP64 are built here, unless they are more than 1 GiB and the
+ * plan is past the scratch of fmm_energy_forces_noalloc: then fmm_plan_config
+ * or the first evaluation builds what the plan's mode needs.
  * On success *out owns them until fmm_destroy.  On failure *out is NULL.
  */
 fmm_status fmm_plan(double box, int levels, int p, fmm_plan_t *out);

@@ -556,6 +556,7 @@ static fmm_status ensure_m2l_ops(fmm_plan_t pl, bool want64 = false) {
 }
 
 static fmm_status ensure_side_streams(fmm_plan_t pl);
+static size_t noalloc_bytes(fmm_plan_t pl, int64_t n);
 
 // member: a box of a batch plan (or an autotuning candidate for one), which
 // never forks and so gets no side streams
@@ -636,12 +637,13 @@ extern "C" fmm_status fmm_plan(double box, int levels, int p, fmm_plan_t *out) {
     // the operators of the default precision are uploaded with the plan
     // (fmm_plan_config and fmm_plan_tuning add what a new mode needs), so an
     // evaluation allocates only its per-call workspace.  Block sets of more
-    // than 1 GiB wait for fmm_plan_config or the first evaluation: a program
-    // that goes on to another precision would never use them, and no plan that
-    // large is within the fixed scratch of fmm_energy_forces_noalloc.
+    // than 1 GiB wait for fmm_plan_config or the first evaluation (a program
+    // that goes on to another precision would never use them), except in plans
+    // within the fixed scratch of fmm_energy_forces_noalloc, which never builds
+    // any (levels 4, p = 14: 1.16 GiB of blocks, 110 MiB of the 128)
     size_t blocks = 0;
     for (int l = 1; l <= conv_levels(*out); ++l) blocks += conv_op_bytes(l, p, 8);
-    if (blocks > ((size_t)1 << 30)) return FMM_OK;
+    if (blocks > ((size_t)1 << 30) && noalloc_bytes(*out, 1) > kNoAllocScratchBytes) return FMM_OK;
     if ((st = ensure_m2l_ops(*out, false)) != FMM_OK) {
         g_plan_error = (*out)->err;
         fmm_destroy(*out);
@@ -819,6 +821,17 @@ static void atom_layout(fmm_plan_t pl, int64_t n, std::vector<WsItem> &v) {
     v.push_back({&pl->mask_s, nn, false});
     v.push_back({&pl->nfsc, sizeof(double) * nn, false});
     v.push_back({&pl->nfdl, sizeof(double) * nn, false});
+}
+
+// bytes of the fixed scratch that an evaluation of n atoms takes
+static size_t noalloc_bytes(fmm_plan_t pl, int64_t n) {
+    std::vector<WsItem> items;
+    tree_layout(pl, items);
+    atom_layout(pl, n, items);
+    size_t need = 0;
+    for (const WsItem &w : items)
+        if (w.eval) need = (need + 255) / 256 * 256 + w.bytes;
+    return need;
 }
 
 static fmm_status ensure_workspace(fmm_plan_t pl, int64_t n) {
@@ -1225,12 +1238,7 @@ extern "C" fmm_status fmm_energy_forces_noalloc(fmm_plan_t pl, int64_t n, const 
     if (pl->device < 0 || pl->device >= 64 || !g_scratch_ptr[pl->device])
         return hip_fail(pl, pl->device >= 0 && pl->device < 64 ? g_scratch_err[pl->device] : hipErrorInvalidDevice,
                         "fmm_energy_forces_noalloc: device address of the scratch array");
-    std::vector<WsItem> items;
-    tree_layout(pl, items);
-    atom_layout(pl, n, items);
-    size_t need = 0;
-    for (const WsItem &w : items)
-        if (w.eval) need = (need + 255) / 256 * 256 + w.bytes;
+    const size_t need = noalloc_bytes(pl, n);
     if (need > kNoAllocScratchBytes)
         return fail(pl, FMM_ERR_INVALID,
                     "fmm_energy_forces_noalloc: " + std::to_string(n) + " atoms on this plan need " +
@@ -1239,6 +1247,9 @@ extern "C" fmm_status fmm_energy_forces_noalloc(fmm_plan_t pl, int64_t n, const 
     if (!m2l_ops_ready(pl, false))
         return fail(pl, FMM_ERR_STATE, "fmm_energy_forces_noalloc: the operators of the current mode are not on the "
                                        "device (fmm_plan, fmm_plan_config and fmm_plan_tuning upload them)");
+    std::vector<WsItem> items;
+    tree_layout(pl, items);
+    atom_layout(pl, n, items);
     char *base = static_cast<char *>(g_scratch_ptr[pl->device]);
     ScratchViews views;
     size_t at = 0;

@@ -162,9 +162,26 @@ static void batch_replay() {
     fmm_destroy(plan);
 }
 
+// A new plan within the fixed scratch has its operators, whatever they take.
+static void plan_then_noalloc() {
+    const int sizes[][2] = {{4, 13}, {4, 14}, {4, 15}, {3, 19}, {3, 20}, {2, 20}, {5, 4}};  // levels, p
+    double *pos = device(300), *q = device(100), e;
+    for (const auto &c : sizes) {
+        fmm_plan_t plan = nullptr;
+        CHECK(fmm_plan(20.0, c[0], c[1], &plan) == FMM_OK);
+        const fmm_status st = fmm_energy_forces_noalloc(plan, 100, pos, q, &e, nullptr, nullptr);
+        if (st != FMM_OK) {
+            std::printf("levels %d p %d: %s\n", c[0], c[1], fmm_last_error(plan));
+            ++bad;
+        }
+        fmm_destroy(plan);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
+    else if (c == "plan_then_noalloc") plan_then_noalloc();
     else {
         std::printf("no such case\n");
         return 2;

@@ -1,5 +1,6 @@
-"""Batches whose boxes change size between calls: a box's workspace grows and moves,
-and every pass has to work on the new one."""
+"""Plans whose workspace or operators are not where the last call left them.  Batches
+whose boxes change size between calls: a box's workspace grows and moves,
+and every pass has to work on the new one.  The first call of a plan."""
 import numpy as np
 import pytest
 
@@ -49,3 +50,15 @@ def test_batch_uv_after_a_larger_batch(fmm, prec, scheme):
     want = both(plan(), c)
     np.testing.assert_array_equal(got[0], want[0])
     np.testing.assert_array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("levels,p", [(4, 14), (3, 20)])
+def test_new_plan_without_allocation(fmm, levels, p):
+    # operators of more than 1 GiB in FP64: there without another call before
+    import torch
+    pos, q = workloads.random_charges(500, 20.0, seed=930, net=1.0)
+    plan = fmm.fmm_plan(20.0, levels, p)
+    f = torch.empty((500, 3), dtype=torch.float64, device="cuda")
+    e = fmm.fmm_energy_forces_noalloc(plan, _t(pos), _t(q), forces=f)
+    want = fmm.fmm_energy_forces(plan, _t(pos), _t(q))
+    assert e == want[0] and bool((f == want[1]).all())

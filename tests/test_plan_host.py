@@ -34,3 +34,7 @@ def check(tmp_path_factory):
 
 def test_batch_symmetric_pass_is_not_a_graph_of_old_workspaces(check):
     assert check("batch_replay") == (0, "ok")
+
+
+def test_new_plan_serves_the_call_that_may_not_allocate(check):
+    assert check("plan_then_noalloc") == (0, "ok")
