@@ -411,10 +411,17 @@ static bool conv_ready(fmm_plan_t pl, int levels) {
         if (!pl->op->conv_ops[l][l <= top].ptr) return false;
     return true;
 }
+// (sets of several buffers: all of them, as the memory may end between two)
+static bool alias_ready(const OpSet &o) {
+    for (int i = 0; i < 2; ++i)
+        if (!o.alias_ops[i].ptr || !o.alias_il[i].ptr || !o.alias_off[i].ptr) return false;
+    return true;
+}
 static bool m2l_ops_ready(fmm_plan_t pl, bool want64) {
     const OpNeeds n = m2l_needs(pl, want64);
-    return conv_ready(pl, n.conv) && (!n.f64 || pl->op->ops64.ptr) && (!n.alias || pl->op->alias_ops[0].ptr) &&
-           (!n.f32 || pl->op->ops32.ptr) && (!n.bf || pl->op->opsbf.ptr) && (!n.f16 || pl->op->ops16.ptr);
+    return conv_ready(pl, n.conv) && (!n.f64 || pl->op->ops64.ptr) && (!n.alias || alias_ready(*pl->op)) &&
+           (!n.f32 || pl->op->ops32.ptr) && (!n.bf || pl->op->opsbf.ptr) &&
+           (!n.f16 || (pl->op->ops16.ptr && pl->op->scale16.ptr));
 }
 
 // Builds the blocks of the convolution levels that are missing (on the GPU,
@@ -481,7 +488,7 @@ static fmm_status ensure_m2l_ops(fmm_plan_t pl, bool want64 = false) {
     std::vector<double> rm;
     build_m2l_all(pl->p, pl->op->offs, rm);
     const size_t ne = m2l_ops_elems<float>(pl->p);
-    if (need16 && !pl->op->ops16.ptr) {
+    if (need16 && !(pl->op->ops16.ptr && pl->op->scale16.ptr)) {
         const size_t nh = m2l_split16_ops_elems(pl->p);
         std::vector<uint16_t> sw(nh);
         std::vector<float> sc((size_t)2 * pl->Kp);
@@ -499,7 +506,7 @@ static fmm_status ensure_m2l_ops(fmm_plan_t pl, bool want64 = false) {
         if (!pl->op->opsbf.ensure(nb * sizeof(uint16_t))) return fail(pl, FMM_ERR_NOMEM, "M2L operator allocation");
         HIPCHK(pl, hipMemcpy(pl->op->opsbf.ptr, sw.data(), nb * sizeof(uint16_t), hipMemcpyHostToDevice), "M2L upload");
     }
-    if (needalias && !pl->op->alias_ops[0].ptr) {
+    if (needalias && !alias_ready(*pl->op)) {
         // On a grid of n <= 4 cells per axis the 875 offsets t of a parity
         // class reach only n^3 distinct source cells (t modulo n), so
         //   sum_t O_t M(c + t) = sum_d (sum_{t = d mod n} O_t) M(c + d):
@@ -845,6 +852,7 @@ static fmm_status ensure_workspace(fmm_plan_t pl, int64_t n) {
     if (n > pl->cap_n) {
         v.clear();
         atom_layout(pl, n, v);
+        pl->cap_n = -1;  // after a failure some buffers are gone: a smaller call needs them back
         for (const WsItem &w : v)
             if (!w.buf->ensure(w.bytes)) return fail(pl, FMM_ERR_NOMEM, "per-atom workspace allocation");
         pl->cap_n = n;

@@ -19,6 +19,7 @@ static struct Fake {
     uintptr_t next = (uintptr_t)1 << 44;
     std::map<uintptr_t, size_t> live;
     long launched = 0, captured = 0, graphs = 0;
+    long allocations_left = -1;  // -1: no limit
     bool capturing = false;
     dim3 grid, block;
     size_t shared = 0;
@@ -40,7 +41,8 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) {
 hipError_t hipMalloc(void **p, size_t b) {
     *p = nullptr;
     if (fk.capturing) return hipErrorStreamCaptureUnsupported;
-    if (b > fk.total - fk.used) return hipErrorOutOfMemory;
+    if (b > fk.total - fk.used || fk.allocations_left == 0) return hipErrorOutOfMemory;
+    if (fk.allocations_left > 0) --fk.allocations_left;
     fk.used += b;
     fk.live[fk.next] = b;
     *p = (void *)fk.next;
@@ -178,10 +180,45 @@ static void plan_then_noalloc() {
     }
 }
 
+// After a call that found no memory, smaller calls have all their buffers.
+static void call_after_no_memory() {
+    double *pos = device(3), *q = device(1), e, u;
+    uint32_t *keys = (uint32_t *)device(1000);
+    fmm_plan_t plan = nullptr;
+    CHECK(fmm_plan(20.0, 3, 4, &plan) == FMM_OK);
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    fk.allocations_left = 0;
+    CHECK(fmm_energy_forces(plan, 2000, pos, q, &e, nullptr, nullptr) == FMM_ERR_NOMEM);
+    fk.allocations_left = -1;
+    CHECK(fmm_bin(plan, 1000, pos, keys, nullptr, nullptr) == FMM_OK);
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    fmm_destroy(plan);
+    // the list operators, with memory for k of their buffers at first: a call that
+    // goes through afterwards has all of them, however many were there before
+    size_t want = 0;
+    for (int k = 12; k >= 0; --k) {
+        CHECK(fmm_plan(20.0, 3, 4, &plan) == FMM_OK);
+        CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+        CHECK(fmm_solute_solvent_energy(plan, (const uint8_t *)q, &u) == FMM_OK);
+        fk.allocations_left = k;
+        (void)fmm_plan_options(plan, FMM_BOUNDARY_CONDUCTING, FMM_UV_SPARSE);
+        (void)fmm_solute_solvent_energy(plan, (const uint8_t *)q, &u);
+        fk.allocations_left = -1;
+        CHECK(fmm_solute_solvent_energy(plan, (const uint8_t *)q, &u) == FMM_OK);
+        if (k == 12) want = fk.live.size();
+        if (fk.live.size() != want) {
+            std::printf("%d allocations first: %zu buffers, not %zu\n", k, fk.live.size(), want);
+            ++bad;
+        }
+        fmm_destroy(plan);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
     else if (c == "plan_then_noalloc") plan_then_noalloc();
+    else if (c == "call_after_no_memory") call_after_no_memory();
     else {
         std::printf("no such case\n");
         return 2;

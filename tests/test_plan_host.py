@@ -38,3 +38,7 @@ def test_batch_symmetric_pass_is_not_a_graph_of_old_workspaces(check):
 
 def test_new_plan_serves_the_call_that_may_not_allocate(check):
     assert check("plan_then_noalloc") == (0, "ok")
+
+
+def test_calls_after_one_without_memory(check):
+    assert check("call_after_no_memory") == (0, "ok")
