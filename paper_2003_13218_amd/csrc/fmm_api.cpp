@@ -62,6 +62,7 @@ struct OpSet {
     // convolution form of the M2L: coefficient table, operators of the
     // reflection representatives and their index, and per level its columns'
     // table, cosines and blocks ([0] FP32, [1] FP64); conv_no: no memory for them
+    // since the last fmm_plan_config or fmm_plan_tuning
     DeviceBuf conv_tab, conv_reps, conv_index, conv_pair[kConvMaxLevel + 1], conv_trig[kConvMaxLevel + 1];
     DeviceBuf conv_ops[kConvMaxLevel + 1][2];
     bool conv_no[kConvMaxLevel + 1][2] = {};
@@ -372,8 +373,10 @@ static int upper_m2l_levels(fmm_plan_t pl) {
 // 5.9 ms, convolution 0.7 ms in FP32; 13.4 and 1.1 ms in FP64), so it is taken
 // wherever the blocks (their bytes grow with 8^level K^2) fit: levels up
 // to 6 (lines of 64 cells in registers), at most a quarter of the device's
-// memory and 64 GiB for a level (p = 20 at level 6 in FP64: 112 GB).  Levels
-// 1 .. 4 go together or not at all.  The BF16 mode keeps the lists: its
+// memory and 64 GiB for a level (p = 20 at level 6 in FP64: 113 GB), and at most
+// half of what is free when they are built.  Levels 1 .. 4 go together or not at
+// all.  Blocks are what a plan can do without: a workspace that finds no memory
+// takes theirs (conv_give_back).  The BF16 mode keeps the lists: its
 // operands are that mode's point.
 static int conv_levels(fmm_plan_t pl) {
     if (pl->prec == FMM_MIXED_BF16_M2L) return 0;
@@ -424,9 +427,36 @@ static bool m2l_ops_ready(fmm_plan_t pl, bool want64) {
            (!n.f16 || (pl->op->ops16.ptr && pl->op->scale16.ptr));
 }
 
+// Frees blocks: those that the plan's mode does not use, else all of them, which
+// leaves its levels to the lists.  False if there are none.  Only between
+// evaluations (they all wait for the device before they return).
+static bool conv_give_back(fmm_plan_t pl) {
+    OpSet &o = *pl->op;
+    const int top = top_fp64_levels(pl), cl = conv_levels(pl);
+    bool freed = false;
+    auto give = [&](int l, int d) {
+        freed = freed || o.conv_ops[l][d].ptr;
+        o.conv_ops[l][d].release();
+    };
+    for (int l = 1; l <= kConvMaxLevel; ++l)
+        for (int d = 0; d < 2; ++d)
+            if (l > cl || d != (l <= top)) give(l, d);
+    if (freed) return true;
+    for (int l = 1; l <= kConvMaxLevel; ++l)
+        for (int d = 0; d < 2; ++d) {
+            give(l, d);
+            o.conv_no[l][d] = true;
+        }
+    return freed;
+}
+static void conv_retry(fmm_plan_t pl) {
+    for (auto &no : pl->op->conv_no) no[0] = no[1] = false;
+}
+
 // Builds the blocks of the convolution levels that are missing (on the GPU,
 // from the operators of the reflection representatives) and waits for them.  A
-// level that finds no memory is marked and left to the lists.
+// level that finds no memory is marked and left to the lists, and so are those
+// that go with it.
 static fmm_status ensure_conv_ops(fmm_plan_t pl) {
     OpSet &o = *pl->op;
     const int top = top_fp64_levels(pl);
@@ -459,11 +489,16 @@ static fmm_status ensure_conv_ops(fmm_plan_t pl) {
             e = upload(o.conv_pair[l], pair.data(), sizeof(int32_t) * pair.size());
             if (e == hipSuccess) e = upload(o.conv_trig[l], trig.data(), sizeof(double) * trig.size());
         }
-        if (e == hipSuccess && !o.conv_ops[l][d].ensure(conv_op_bytes(l, pl->p, d ? 8 : 4))) e = hipErrorOutOfMemory;
+        const size_t need = conv_op_bytes(l, pl->p, d ? 8 : 4);
+        size_t avail = 0, total = 0;
+        if (e == hipSuccess && hipMemGetInfo(&avail, &total) == hipSuccess && need > avail / 2) e = hipErrorOutOfMemory;
+        if (e == hipSuccess && !o.conv_ops[l][d].ensure(need)) e = hipErrorOutOfMemory;
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
             o.conv_no[l][d] = true;
-            continue;
+            if (conv_levels(pl) == 0)
+                for (int k = 1; k < l; ++k) o.conv_ops[k][k <= top].release();
+            break;
         }
         if (e == hipSuccess)
             e = launch_conv_build(l, pl->p, o.conv_reps.as<double>(), o.conv_index.as<int32_t>(),
@@ -675,9 +710,11 @@ extern "C" fmm_status fmm_plan_config(fmm_plan_t pl, int precision, double kappa
             b->have_state = false;
         }
         batch_drop_graphs(pl);
+        conv_retry(pl);
         return FMM_OK;
     }
     pl->prec = precision;
+    conv_retry(pl);
     pl->stream = (hipStream_t)hip_stream;
     pl->have_state = false;
     if (kappa > 0.0 && kappa != pl->kappa) {
@@ -702,6 +739,7 @@ extern "C" fmm_status fmm_plan_tuning(fmm_plan_t pl, int fp64_levels, int p2p_gr
     };
     set(pl);
     for (fmm_plan_t b : pl->sub) set(b);
+    conv_retry(pl);
     if (pl->is_batch) {
         pl->batch_state = false;
         batch_drop_graphs(pl);
@@ -841,20 +879,29 @@ static size_t noalloc_bytes(fmm_plan_t pl, int64_t n) {
     return need;
 }
 
+// items in memory; where there is none left, in that of the convolution's blocks
+static bool ensure_items(fmm_plan_t pl, const std::vector<WsItem> &items) {
+    for (const WsItem &w : items)
+        while (!w.buf->ensure(w.bytes)) {
+            (void)hipGetLastError();
+            if (!conv_give_back(pl)) return false;
+        }
+    return true;
+}
+
+// Before ensure_m2l_ops, which builds what a workspace without memory took
 static fmm_status ensure_workspace(fmm_plan_t pl, int64_t n) {
     std::vector<WsItem> v;
     if (!pl->tree_ready) {
         tree_layout(pl, v);
-        for (const WsItem &w : v)
-            if (!w.buf->ensure(w.bytes)) return fail(pl, FMM_ERR_NOMEM, "tree workspace allocation");
+        if (!ensure_items(pl, v)) return fail(pl, FMM_ERR_NOMEM, "tree workspace allocation");
         pl->tree_ready = true;
     }
     if (n > pl->cap_n) {
         v.clear();
         atom_layout(pl, n, v);
         pl->cap_n = -1;  // after a failure some buffers are gone: a smaller call needs them back
-        for (const WsItem &w : v)
-            if (!w.buf->ensure(w.bytes)) return fail(pl, FMM_ERR_NOMEM, "per-atom workspace allocation");
+        if (!ensure_items(pl, v)) return fail(pl, FMM_ERR_NOMEM, "per-atom workspace allocation");
         pl->cap_n = n;
     }
     return FMM_OK;
@@ -1911,12 +1958,17 @@ extern "C" fmm_status fmm_energy_forces_batch(fmm_plan_t pl, const int64_t *offs
         fmm_plan_t b = pl->sub[w];
         b->have_state = false;
         const int64_t n = offsets[w + 1] - offsets[w];
-        if (n == 0) continue;
-        if ((st = ensure_workspace(b, n)) != FMM_OK || (st = ensure_m2l_ops(b)) != FMM_OK) {
+        if (n > 0 && (st = ensure_workspace(b, n)) != FMM_OK) {
             pl->err = "box " + std::to_string(w) + ": " + b->err;
             return st;
         }
     }
+    // after every workspace, which may take the operators' memory
+    for (size_t w = 0; w < nb; ++w)
+        if (offsets[w + 1] > offsets[w] && (st = ensure_m2l_ops(pl->sub[w])) != FMM_OK) {
+            pl->err = "box " + std::to_string(w) + ": " + pl->sub[w]->err;
+            return st;
+        }
     if ((st = batch_inputs(pl)) != FMM_OK) return st;
     st = batch_branches(pl, offsets, [&](size_t w) -> fmm_status {
         fmm_plan_t b = pl->sub[w];

@@ -214,11 +214,68 @@ static void call_after_no_memory() {
     }
 }
 
+static int64_t conv_levels(fmm_plan_t plan) {
+    int64_t info[FMM_INFO_COUNT];
+    CHECK(fmm_plan_info(plan, info, FMM_INFO_COUNT) == FMM_OK);
+    return info[11];
+}
+
+// Memory of the convolution's operators goes to workspaces that need it.
+static void short_of_memory() {
+    double *pos = device(3), *q = device(1), e;
+    uint32_t *keys = (uint32_t *)device(1000);
+    void *others = nullptr;
+    CHECK(hipMalloc(&others, fk.total - fk.used - ((size_t)22 << 30)) == hipSuccess);
+    fmm_plan_t plan = nullptr;
+    CHECK(fmm_plan(100.0, 6, 12, &plan) == FMM_OK);
+    CHECK(fmm_plan_config(plan, FMM_MIXED, 0.0, nullptr) == FMM_OK);
+    CHECK(conv_levels(plan) == 6);  // 10 of the 22 GiB
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    CHECK(conv_levels(plan) == 6);
+    // 50 million atoms: 12 GiB of workspace beside the 3 of the tree
+    CHECK(fmm_energy_forces(plan, 50000000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    CHECK(conv_levels(plan) == 0);
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    // more than there is: refused, and smaller calls work again
+    CHECK(fmm_energy_forces(plan, 400000000, pos, q, &e, nullptr, nullptr) == FMM_ERR_NOMEM);
+    CHECK(fmm_bin(plan, 1000, pos, keys, nullptr, nullptr) == FMM_OK);
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    // memory is back: so are the operators, once the plan is configured
+    CHECK(hipFree(others) == hipSuccess);
+    CHECK(fmm_plan_config(plan, FMM_MIXED, 0.0, nullptr) == FMM_OK);
+    CHECK(conv_levels(plan) == 6);
+    fmm_destroy(plan);
+
+    // a batch: the second box's workspace takes what the first would use
+    const double box[2] = {100.0, 100.0};
+    const int levels[2] = {6, 5};
+    const int64_t off[3] = {0, 1000, 50001000};
+    double energies[2];
+    CHECK(hipMalloc(&others, fk.total - fk.used - ((size_t)22 << 30)) == hipSuccess);
+    CHECK(fmm_plan_batch(2, box, nullptr, levels, 12, &plan) == FMM_OK);
+    CHECK(fmm_plan_config(plan, FMM_MIXED, 0.0, nullptr) == FMM_OK);
+    const int64_t small[3] = {0, 1000, 2000};
+    CHECK(fmm_energy_forces_batch(plan, small, pos, q, energies, nullptr) == FMM_OK);
+    CHECK(fmm_energy_forces_batch(plan, off, pos, q, energies, nullptr) == FMM_OK);
+    fmm_destroy(plan);
+    // operators take at most half of what is free
+    CHECK(hipFree(others) == hipSuccess);
+    CHECK(hipMalloc(&others, fk.total - fk.used - ((size_t)12 << 30)) == hipSuccess);
+    CHECK(fmm_plan(100.0, 6, 12, &plan) == FMM_OK);
+    CHECK(fmm_plan_config(plan, FMM_MIXED, 0.0, nullptr) == FMM_OK);
+    CHECK(conv_levels(plan) == 5);
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    fmm_destroy(plan);
+    CHECK(hipFree(others) == hipSuccess);
+    CHECK(fk.used == sizeof(double) * (3 + 1 + 1000));
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
     else if (c == "plan_then_noalloc") plan_then_noalloc();
     else if (c == "call_after_no_memory") call_after_no_memory();
+    else if (c == "short_of_memory") short_of_memory();
     else {
         std::printf("no such case\n");
         return 2;

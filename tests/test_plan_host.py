@@ -42,3 +42,7 @@ def test_new_plan_serves_the_call_that_may_not_allocate(check):
 
 def test_calls_after_one_without_memory(check):
     assert check("call_after_no_memory") == (0, "ok")
+
+
+def test_workspaces_take_the_memory_of_operators(check):
+    assert check("short_of_memory") == (0, "ok")
