@@ -188,7 +188,8 @@ typedef enum {
  *              u and v, so every scheme returns the same value up to the
  *              truncation and rounding of the far field.
  * On a batch plan the options apply to every box.  FMM_ERR_INVALID for
- * values outside the enums.
+ * values outside the enums.  SPARSE uploads its operators here; where that
+ * fails (FMM_ERR_NOMEM) the options are set, and the first pass tries again.
  */
 fmm_status fmm_plan_options(fmm_plan_t plan, int boundary, int uv_scheme);
 

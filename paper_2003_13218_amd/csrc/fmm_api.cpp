@@ -797,10 +797,13 @@ extern "C" fmm_status fmm_plan_options(fmm_plan_t pl, int boundary, int uv_schem
         pl->have_state = false;
     }
     // the sparse pass needs the list operators: uploaded here rather than by
-    // its first call, which builds them (and reports) if this fails
+    // its first call, which tries again if this fails
+    if (!(uv_scheme & FMM_UV_SPARSE)) return FMM_OK;
+    HIPCHK(pl, hipSetDevice(pl->device), "hipSetDevice");
     fmm_plan_t first = pl->is_batch ? pl->sub[0] : pl;
-    if ((uv_scheme & FMM_UV_SPARSE) && hipSetDevice(pl->device) == hipSuccess) (void)ensure_m2l_ops(first, true);
-    return FMM_OK;
+    const fmm_status st = ensure_m2l_ops(first, true);
+    if (st != FMM_OK && pl->is_batch) pl->err = first->err;
+    return st;
 }
 
 // ---------------------------------------------------------------------------

@@ -270,12 +270,35 @@ static void short_of_memory() {
     CHECK(fk.used == sizeof(double) * (3 + 1 + 1000));
 }
 
+// Operators that fmm_plan_options cannot upload are its failure, not a later call's.
+static void options_without_memory() {
+    const double box[2] = {20.0, 20.0};
+    const int levels[2] = {2, 2};
+    double *pos = device(3), *q = device(1), e, u;
+    fmm_plan_t single = nullptr, batch = nullptr;
+    CHECK(fmm_plan(20.0, 3, 4, &single) == FMM_OK);
+    CHECK(fmm_plan_batch(2, box, nullptr, levels, 4, &batch) == FMM_OK);
+    for (fmm_plan_t plan : {single, batch}) {
+        fk.allocations_left = 0;
+        CHECK(fmm_plan_options(plan, FMM_BOUNDARY_VACUUM, FMM_UV_SYMMETRIC) == FMM_OK);
+        CHECK(fmm_plan_options(plan, FMM_BOUNDARY_VACUUM, FMM_UV_SPARSE) == FMM_ERR_NOMEM);
+        CHECK(std::strlen(fmm_last_error(plan)) > 0);
+        fk.allocations_left = -1;
+        CHECK(fmm_plan_options(plan, FMM_BOUNDARY_VACUUM, FMM_UV_SPARSE) == FMM_OK);
+    }
+    CHECK(fmm_energy_forces(single, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    CHECK(fmm_solute_solvent_energy(single, (const uint8_t *)q, &u) == FMM_OK);
+    fmm_destroy(single);
+    fmm_destroy(batch);
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
     else if (c == "plan_then_noalloc") plan_then_noalloc();
     else if (c == "call_after_no_memory") call_after_no_memory();
     else if (c == "short_of_memory") short_of_memory();
+    else if (c == "options_without_memory") options_without_memory();
     else {
         std::printf("no such case\n");
         return 2;
