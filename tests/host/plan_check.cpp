@@ -19,6 +19,7 @@ static struct Fake {
     uintptr_t next = (uintptr_t)1 << 44;
     std::map<uintptr_t, size_t> live;
     long launched = 0, captured = 0, graphs = 0;
+    int64_t widest = 0;  // wavefronts of the largest launch
     long allocations_left = -1;  // -1: no limit
     bool capturing = false;
     dim3 grid, block;
@@ -122,6 +123,8 @@ hipError_t hipLaunchKernel(const void *, dim3 g, dim3 b, void **, size_t, hipStr
         std::exit(1);
     }
     ++(fk.capturing ? fk.captured : fk.launched);
+    const int64_t waves = (int64_t)g.x * g.y * g.z * ((b.x * b.y * b.z + 63) / 64);
+    if (waves > fk.widest) fk.widest = waves;
     return hipSuccess;
 }
 }
@@ -292,6 +295,26 @@ static void options_without_memory() {
     fmm_destroy(batch);
 }
 
+// The near field of few crowded leaves is split into a wavefront for every 8 of its
+// targets, up to 64 a leaf (the other launches of these calls are smaller).
+static void crowded_leaves() {
+    const int64_t cases[][3] = {{1, 3000, 8 * 47}, {2, 8000, 64 * 16}, {2, 30000, 64 * 59}, {2, 60000, 64 * 64}};
+    double *pos = device(3), *q = device(1), e;
+    for (const auto &c : cases)
+        for (int prec : {FMM_FP64, FMM_MIXED}) {
+            fmm_plan_t plan = nullptr;
+            CHECK(fmm_plan(20.0, (int)c[0], 2, &plan) == FMM_OK);
+            CHECK(fmm_plan_config(plan, prec, 0.0, nullptr) == FMM_OK);
+            fk.widest = 0;
+            CHECK(fmm_energy_forces(plan, c[1], pos, q, &e, nullptr, nullptr) == FMM_OK);
+            if (fk.widest < c[2]) {
+                std::printf("levels %d, %d atoms: %d wavefronts\n", (int)c[0], (int)c[1], (int)fk.widest);
+                ++bad;
+            }
+            fmm_destroy(plan);
+        }
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
@@ -299,6 +322,7 @@ int main(int argc, char **argv) {
     else if (c == "call_after_no_memory") call_after_no_memory();
     else if (c == "short_of_memory") short_of_memory();
     else if (c == "options_without_memory") options_without_memory();
+    else if (c == "crowded_leaves") crowded_leaves();
     else {
         std::printf("no such case\n");
         return 2;

@@ -50,3 +50,7 @@ def test_workspaces_take_the_memory_of_operators(check):
 
 def test_options_report_operators_that_do_not_fit(check):
     assert check("options_without_memory") == (0, "ok")
+
+
+def test_crowded_leaves_fill_the_chip(check):
+    assert check("crowded_leaves") == (0, "ok")
