@@ -138,8 +138,8 @@ fmm_status fmm_plan_config(fmm_plan_t plan, int precision, double kappa, void *h
  *                evaluation.  Ignored in FMM_FP64 (everything is FP64).
  *                -1 keeps the current value.
  *   p2p_groups   source groups of the near-field kernel (1, 2, 4, 8, 16: the
- *                atoms of a leaf are split in target chunks of at most 128 /
- *                groups, between 64 and 8), or 0 to choose from the mean leaf
+ *                atoms of a leaf are split in target chunks of at most 64 /
+ *                groups, 8 for 16 groups), or 0 to choose from the mean leaf
  *                occupancy (default); -1 keeps the current value.  Changes
  *                the schedule only: results are identical up to the order of
  *                sums.

@@ -911,7 +911,7 @@ static fmm_status ensure_workspace(fmm_plan_t pl, int64_t n) {
 }
 
 // Source groups of the near field: the largest chunk of targets of a wavefront
-// is 128 / groups.  Sparse leaves fit one chunk of 16 or less anyway, and the few
+// is 64 / groups, at least 8.  Sparse leaves fit one chunk of 16 or less anyway, and the few
 // fuller ones are best done in one (11 atoms a leaf, 262,144 leaves: 32 targets
 // 3.62 ms, 16 3.74); crowded leaves take 16 (30 a leaf, 32,768 leaves: 2.03 ms, 32
 // 2.10, 8 2.21), and 8 where 16 would leave the chip with fewer than two
@@ -920,8 +920,8 @@ static fmm_status ensure_workspace(fmm_plan_t pl, int64_t n) {
 // alone, for the same results (24 windows of 512 leaves: 5.54, 5.59, 6.98 ms).
 static int p2p_groups(int64_t n, int levels) {
     const double leaves = (double)level_cells(levels), occ = (double)n / leaves;
-    if (occ <= 16.0) return 4;
-    return leaves * std::ceil(occ / 16.0) < 16384.0 ? 16 : 8;
+    if (occ <= 16.0) return 2;
+    return leaves * std::ceil(occ / 16.0) < 16384.0 ? 8 : 4;
 }
 static int plan_groups(fmm_plan_t pl, int64_t n) { return pl->p2p_g ? pl->p2p_g : p2p_groups(n, pl->levels); }
 
@@ -1149,7 +1149,7 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
         // are many; few crowded ones are split further, until the chip's slots are
         // taken twice (60,000 atoms, FP32: 64 leaves 22.0 ms with 8, 3.6 with 64;
         // 512 leaves 0.68 and 0.68; 3,000 atoms, 8 leaves 2.9 and 1.0)
-        const int chunk = std::max(8, std::min(64, 128 / groups));
+        const int chunk = std::max(8, 64 / groups);
         const double occ = (double)n / (double)nleaf;
         int nsplit = (int)std::ceil(occ / chunk);
         while (nsplit < 8 && nleaf * nsplit < 65536) nsplit *= 2;
@@ -2154,7 +2154,7 @@ static fmm_status batch_set_box(fmm_plan_t pl, size_t w, int L, int g) {
 // Autotuner: for every non-empty box, time whole evaluations (energy and
 // forces, hipEvent-timed on the box's stream after one warm-up) for the tree
 // depths L-1, L, L+1 around the current one and the P2P source-group counts
-// 2, 4, 8, and keep the fastest configuration.  Scratch plans share the
+// 2, 4, 8 (all that p2p_groups chooses from), and keep the fastest configuration.  Scratch plans share the
 // box-independent operators.
 extern "C" fmm_status fmm_autotune_batch(fmm_plan_t pl, const int64_t *offsets, const double *pos, const double *q,
                                          double *forces_scratch) {

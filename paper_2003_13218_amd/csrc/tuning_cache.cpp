@@ -2,9 +2,9 @@
 //
 // A text file of one line per tuned batch,
 //   <key> TAB <depth of every box, comma-separated> TAB <P2P groups, same> LF
-// where the key names what the timings depend on: the device architecture,
-// the order, the precision mode, the FP64 top levels and every box's edge and
-// atom count.  Lines are only appended, each with one write; the last valid
+// where the key names what the timings depend on: the kernels (a version, raised
+// when they change which settings are fast), the device architecture, the order,
+// the precision mode, the FP64 top levels and every box's edge and atom count.  Lines are only appended, each with one write; the last valid
 // line for a key wins, and lines that do not parse (a torn or foreign line)
 // are skipped.
 #include <algorithm>
@@ -23,7 +23,7 @@ std::string tuning_cache_key(const std::string &arch, int p, int prec, int fp64_
         if (c == '\t' || c == '\n' || c == '\r' || c == ' ') c = '_';
     char buf[96];
     std::snprintf(buf, sizeof buf, " p=%d prec=%d fp64_levels=%d boxes=", p, prec, fp64_levels);
-    std::string key = "fmm-autotune-1 arch=" + a + buf;
+    std::string key = "fmm-autotune-2 arch=" + a + buf;
     for (size_t w = 0; w < nbox; ++w) {
         std::snprintf(buf, sizeof buf, "%s%.17g:%lld", w ? "," : "", box[w], (long long)natoms[w]);
         key += buf;

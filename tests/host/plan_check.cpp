@@ -315,6 +315,26 @@ static void crowded_leaves() {
         }
 }
 
+// Settings timed with other kernels are not taken from the autotuner's cache file.
+static void old_cache_line(const char *path) {
+    const double box[2] = {20.0, 21.0};
+    const int levels[2] = {2, 2};
+    const int64_t off[3] = {0, 300, 700};
+    double *pos = device(3), *q = device(1);
+    FILE *fp = std::fopen(path, "wb");
+    CHECK(fp != nullptr);
+    std::fprintf(fp, "fmm-autotune-1 arch=gfx950 p=4 prec=0 fp64_levels=3 boxes=20:300,21:400\t3,3\t8,8\n");
+    std::fclose(fp);
+    int hit = 1;
+    fmm_plan_t plan = nullptr;
+    CHECK(fmm_plan_batch(2, box, nullptr, levels, 4, &plan) == FMM_OK);
+    CHECK(fmm_autotune_batch_cached(plan, off, pos, q, nullptr, path, &hit) == FMM_OK);
+    CHECK(hit == 0);
+    CHECK(fmm_autotune_batch_cached(plan, off, pos, q, nullptr, path, &hit) == FMM_OK);
+    CHECK(hit == 1);  // the line that the first call wrote
+    fmm_destroy(plan);
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
@@ -323,6 +343,7 @@ int main(int argc, char **argv) {
     else if (c == "short_of_memory") short_of_memory();
     else if (c == "options_without_memory") options_without_memory();
     else if (c == "crowded_leaves") crowded_leaves();
+    else if (c == "old_cache_line" && argc > 2) old_cache_line(argv[2]);
     else {
         std::printf("no such case\n");
         return 2;

@@ -1,5 +1,5 @@
 """Few crowded leaves: the near field with more than 8 wavefronts a leaf, against the
-oracle's direct sums in 64 bits."""
+oracle's direct sums in 64 bits.  The chunks that the near field chooses by itself."""
 import numpy as np
 import pytest
 
@@ -41,3 +41,20 @@ def test_crowded_leaves(fmm, levels, n, prec, tol_phi, tol_field):
     print(f"levels {levels} n {n} prec {prec}: phi {ep:.2e}, field {ef:.2e}")
     grow = max(1.0, (125 * n / 8 ** levels / 7500) ** 0.5)
     assert ep < tol_phi * grow and ef < tol_field * grow
+
+
+@pytest.mark.parametrize("levels,n", [(2, 300), (2, 1900), (3, 15000), (4, 60000), (4, 123000)])
+def test_default_is_among_the_autotuners_choices(fmm, levels, n):
+    # 5 to 30 atoms a leaf, few and many leaves: the order of sums tells the chunk, and
+    # that of the default is one of those that the autotuner times
+    rng = np.random.default_rng(levels)
+    pos, q = rng.uniform(0, 30.0, (n, 3)), rng.uniform(-1, 1, n)
+    plan = fmm.fmm_plan(30.0, levels, 2)
+    fmm.fmm_plan_config(plan, fmm.FMM_MIXED)
+    field = {}
+    for g in (0, 2, 4, 8):
+        fmm.fmm_plan_tuning(plan, p2p_groups=g)
+        field[g] = fmm.fmm_potential_parts(plan, _t(pos), _t(q))[1]
+    same = [g for g in (2, 4, 8) if bool((field[0] == field[g]).all())]
+    print(f"levels {levels} n {n}: as {same}")
+    assert same

@@ -54,3 +54,7 @@ def test_options_report_operators_that_do_not_fit(check):
 
 def test_crowded_leaves_fill_the_chip(check):
     assert check("crowded_leaves") == (0, "ok")
+
+
+def test_cache_lines_of_other_kernels_are_not_taken(check, tmp_path):
+    assert check("old_cache_line", tmp_path / "autotune.txt") == (0, "ok")
