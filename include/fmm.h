@@ -149,6 +149,16 @@ fmm_status fmm_plan_config(fmm_plan_t plan, int precision, double kappa, void *h
  */
 fmm_status fmm_plan_tuning(fmm_plan_t plan, int fp64_levels, int p2p_groups);
 
+/*
+ * fmm_plan_conv_levels -- finest level whose M2L may run as a convolution
+ *   (0 .. 6, default 6; see fmm_plan), for programs that would rather have its
+ *   operators' memory: the finer levels take the interaction lists, all levels
+ *   where max_level leaves out one of 1 .. 4.  Same results up to the rounding
+ *   of the mode.  On a batch plan it applies to every box.  Clears the cached
+ *   state used by fmm_solute_solvent_energy.  FMM_ERR_INVALID for other values.
+ */
+fmm_status fmm_plan_conv_levels(fmm_plan_t plan, int max_level);
+
 /* Boundary condition at infinity (Appendix A, eq. surfdipole). */
 typedef enum {
     FMM_BOUNDARY_CONDUCTING = 0, /* tin-foil boundary of the Ewald sum (default) */

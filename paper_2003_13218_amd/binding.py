@@ -35,7 +35,7 @@ EXPORTED = (
     "fmm_last_error", "fmm_destroy", "fmm_version", "fmm_plan_batch", "fmm_energy_forces_batch",
     "fmm_solute_solvent_energy_batch", "fmm_autotune_batch", "fmm_batch_levels", "fmm_lambda_energy",
     "fmm_lambda_energy_batch", "fmm_plan_options", "fmm_plan_softcore", "fmm_plan_info", "fmm_plan_tuning",
-    "fmm_energy_forces_noalloc", "fmm_batch_set_tuning", "fmm_autotune_batch_cached",
+    "fmm_energy_forces_noalloc", "fmm_batch_set_tuning", "fmm_autotune_batch_cached", "fmm_plan_conv_levels",
 )
 
 STAGES = ("sort", "gather", "p2m", "m2m", "lattice", "m2l", "m2l_leaf", "l2l", "l2p", "p2p", "final", "total")
@@ -68,6 +68,8 @@ def load():
         lib.fmm_plan_options.restype = ci
         lib.fmm_plan_tuning.argtypes = [vp, ci, ci]
         lib.fmm_plan_tuning.restype = ci
+        lib.fmm_plan_conv_levels.argtypes = [vp, ci]
+        lib.fmm_plan_conv_levels.restype = ci
         lib.fmm_plan_softcore.argtypes = [vp, dbl, dbl, ci]
         lib.fmm_plan_softcore.restype = ci
         lib.fmm_plan_info.argtypes = [vp, vp, ci]
@@ -195,6 +197,11 @@ def fmm_plan_info(plan: Plan) -> dict:
 def fmm_plan_tuning(plan: Plan, fp64_levels: int = -1, p2p_groups: int = -1):
     """Mixed-mode FP64 tree levels and near-field source groups (-1 keeps a value)."""
     _check(load().fmm_plan_tuning(plan.handle, int(fp64_levels), int(p2p_groups)), plan)
+
+
+def fmm_plan_conv_levels(plan: Plan, max_level: int = 6):
+    """Finest level whose M2L may run as a convolution; finer ones take the interaction lists."""
+    _check(load().fmm_plan_conv_levels(plan.handle, int(max_level)), plan)
 
 
 def fmm_plan_softcore(plan: Plan, alpha: float, sigma: float = 1.0, c: int = 6):

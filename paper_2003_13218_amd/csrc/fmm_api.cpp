@@ -105,6 +105,7 @@ struct fmm_plan {
     // the level-0 operator, so it never passes through FP32 arrays
     double t00 = 0.0;
     size_t conv_budget = 0;  // largest block set of a convolution level (see conv_levels)
+    int conv_max = kConvMaxLevel;  // finest level that may take it (fmm_plan_conv_levels)
     int top_fp64 = 3;  // mixed mode: tree levels 1..3 in FP64 (see top_fp64_levels)
     double q_tree = 0.0;  // level-0 monopole of the last fmm_energy_forces tree
     double last_energy = 0.0;  // energy of the last fmm_energy_forces call
@@ -382,7 +383,7 @@ static int conv_levels(fmm_plan_t pl) {
     if (pl->prec == FMM_MIXED_BF16_M2L) return 0;
     const int top = top_fp64_levels(pl);
     int c = 0;
-    for (int l = 1; l <= std::min(pl->levels, kConvMaxLevel); ++l) {
+    for (int l = 1; l <= std::min(pl->levels, pl->conv_max); ++l) {
         const bool d = l <= top;
         if (pl->op->conv_no[l][d] || conv_op_bytes(l, pl->p, d ? 8 : 4) > pl->conv_budget) break;
         c = l;
@@ -740,6 +741,25 @@ extern "C" fmm_status fmm_plan_tuning(fmm_plan_t pl, int fp64_levels, int p2p_gr
     set(pl);
     for (fmm_plan_t b : pl->sub) set(b);
     conv_retry(pl);
+    if (pl->is_batch) {
+        pl->batch_state = false;
+        batch_drop_graphs(pl);
+        return FMM_OK;
+    }
+    HIPCHK(pl, hipSetDevice(pl->device), "hipSetDevice");
+    return ensure_m2l_ops(pl, false);
+}
+
+extern "C" fmm_status fmm_plan_conv_levels(fmm_plan_t pl, int max_level) {
+    if (!pl) return fail(nullptr, FMM_ERR_INVALID, "fmm_plan_conv_levels: plan is NULL");
+    if (max_level < 0 || max_level > kConvMaxLevel)
+        return fail(pl, FMM_ERR_INVALID, "fmm_plan_conv_levels: max_level must be in [0, 6]");
+    auto set = [&](fmm_plan_t b) {
+        b->conv_max = max_level;
+        b->have_state = false;
+    };
+    set(pl);
+    for (fmm_plan_t b : pl->sub) set(b);
     if (pl->is_batch) {
         pl->batch_state = false;
         batch_drop_graphs(pl);
@@ -2135,6 +2155,7 @@ static fmm_status batch_set_box(fmm_plan_t pl, size_t w, int L, int g) {
         fmm_status st = plan_create(cur->box, L, pl->p, pl->op, true, &b);
         if (st != FMM_OK) return fail(pl, st, "box " + std::to_string(w) + ": " + g_plan_error);
         b->top_fp64 = cur->top_fp64;
+        b->conv_max = cur->conv_max;
         b->boundary = cur->boundary;
         b->uv_scheme = cur->uv_scheme;
         b->sc_alpha = cur->sc_alpha;
@@ -2204,6 +2225,7 @@ extern "C" fmm_status fmm_autotune_batch(fmm_plan_t pl, const int64_t *offsets, 
                 break;
             }
             b->top_fp64 = cur->top_fp64;
+            b->conv_max = cur->conv_max;
             b->boundary = cur->boundary;
             b->prec = pl->prec;
             b->stream = pl->sub_stream[w];
