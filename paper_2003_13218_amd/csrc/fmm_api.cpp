@@ -1904,7 +1904,10 @@ static fmm_status check_batch_offsets(fmm_plan_t pl, const int64_t *off) {
 }
 
 // `enqueue(w)` for every non-empty box, each on its own stream, forked from and
-// joined into the batch stream
+// joined into the batch stream.  The joins come after all boxes: the device has
+// few hardware queues, and a wait of the batch stream for one box would hold back
+// the boxes enqueued after it on the same queue (energies and forces of 5 boxes of
+// 3,001 atoms 1.08 -> 0.89 ms, of 24 of 24,000 with e_uv 5.0 -> 4.7).
 template <typename F>
 static fmm_status batch_branches(fmm_plan_t pl, const int64_t *off, F enqueue) {
     hipStream_t cs = pl->stream;
@@ -1920,8 +1923,9 @@ static fmm_status batch_branches(fmm_plan_t pl, const int64_t *off, F enqueue) {
             return st;
         }
         HIPCHK(pl, hipEventRecord(pl->sub_done[w], b->stream), "event record");
-        HIPCHK(pl, hipStreamWaitEvent(cs, pl->sub_done[w], 0), "stream wait");
     }
+    for (size_t w = 0; w < pl->sub.size(); ++w)
+        if (off[w + 1] > off[w]) HIPCHK(pl, hipStreamWaitEvent(cs, pl->sub_done[w], 0), "stream wait");
     return FMM_OK;
 }
 

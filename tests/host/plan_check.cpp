@@ -20,6 +20,8 @@ static struct Fake {
     std::map<uintptr_t, size_t> live;
     long launched = 0, captured = 0, graphs = 0;
     int64_t widest = 0;  // wavefronts of the largest launch
+    hipStream_t watched = nullptr;  // launches so far at the first wait of this stream
+    long waited_at = -1;
     long allocations_left = -1;  // -1: no limit
     bool capturing = false;
     dim3 grid, block;
@@ -81,7 +83,10 @@ hipError_t hipGetSymbolAddress(void **p, const void *) { *p = (void *)((uintptr_
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)std::malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) {
+    if (s == fk.watched && fk.waited_at < 0) fk.waited_at = fk.launched;
+    return hipSuccess;
+}
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
@@ -335,6 +340,30 @@ static void old_cache_line(const char *path) {
     fmm_destroy(plan);
 }
 
+// The batch's stream waits for the boxes once all of them are enqueued.
+static void batch_joins() {
+    const double box[3] = {20.0, 21.0, 22.0};
+    const int levels[3] = {2, 3, 1};
+    const int64_t off[4] = {0, 300, 700, 900};
+    double *pos = device(3), *q = device(1), e[3], u[3];
+    hipStream_t s = nullptr;
+    CHECK(hipStreamCreateWithFlags(&s, 0) == hipSuccess);
+    fmm_plan_t plan = nullptr;
+    CHECK(fmm_plan_batch(3, box, nullptr, levels, 4, &plan) == FMM_OK);
+    CHECK(fmm_plan_config(plan, FMM_FP64, 0.0, s) == FMM_OK);
+    CHECK(fmm_energy_forces_batch(plan, off, pos, q, e, nullptr) == FMM_OK);  // the operators
+    fk.watched = s;
+    CHECK(fmm_energy_forces_batch(plan, off, pos, q, e, nullptr) == FMM_OK);
+    CHECK(fk.waited_at == fk.launched);
+    const long before = fk.launched;
+    fk.waited_at = -1;
+    CHECK(fmm_solute_solvent_energy_batch(plan, (const uint8_t *)q, u) == FMM_OK);
+    CHECK(fk.waited_at - before >= 3 * 8);  // all dense passes; the shared stages follow
+    fk.watched = nullptr;
+    fmm_destroy(plan);
+    CHECK(hipStreamDestroy(s) == hipSuccess);
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
@@ -343,6 +372,7 @@ int main(int argc, char **argv) {
     else if (c == "short_of_memory") short_of_memory();
     else if (c == "options_without_memory") options_without_memory();
     else if (c == "crowded_leaves") crowded_leaves();
+    else if (c == "batch_joins") batch_joins();
     else if (c == "old_cache_line" && argc > 2) old_cache_line(argv[2]);
     else {
         std::printf("no such case\n");

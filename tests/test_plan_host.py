@@ -58,3 +58,7 @@ def test_crowded_leaves_fill_the_chip(check):
 
 def test_cache_lines_of_other_kernels_are_not_taken(check, tmp_path):
     assert check("old_cache_line", tmp_path / "autotune.txt") == (0, "ok")
+
+
+def test_batch_waits_for_its_boxes_after_the_last(check):
+    assert check("batch_joins") == (0, "ok")
