@@ -106,8 +106,8 @@ typedef enum {
  * about 0.42 8^levels K^2 elements of the level's type (27 Kp^2 per triple of
  * wave numbers; 1,000,000 atoms, levels 5, p 12: 1.4 GB in FP32, 2.7 GB in
  * FP64).  A level whose operators would take more than 64 GiB, a quarter of
- * the device's memory or half of what is free takes the interaction lists, and
- * a workspace that finds no memory takes the operators', whose levels then take
+ * the device's memory or (past 64 MiB) half of what is free takes the
+ * interaction lists, and a workspace that finds no memory takes the operators', whose levels then take
  * the lists until the next fmm_plan_config or fmm_plan_tuning.  The
  * operators of FMM_FP64 are built here, unless they are more than 1 GiB and the
  * plan is past the scratch of fmm_energy_forces_noalloc: then fmm_plan_config

@@ -450,6 +450,7 @@ static bool conv_give_back(fmm_plan_t pl) {
         }
     return freed;
 }
+constexpr size_t kConvAsk = (size_t)64 << 20;  // sets up to this size are taken wherever they fit
 static void conv_retry(fmm_plan_t pl) {
     for (auto &no : pl->op->conv_no) no[0] = no[1] = false;
 }
@@ -491,8 +492,9 @@ static fmm_status ensure_conv_ops(fmm_plan_t pl) {
             if (e == hipSuccess) e = upload(o.conv_trig[l], trig.data(), sizeof(double) * trig.size());
         }
         const size_t need = conv_op_bytes(l, pl->p, d ? 8 : 4);
-        size_t avail = 0, total = 0;
-        if (e == hipSuccess && hipMemGetInfo(&avail, &total) == hipSuccess && need > avail / 2) e = hipErrorOutOfMemory;
+        size_t avail = 0, total = 0;  // asking takes longer than building a small set
+        if (e == hipSuccess && need > kConvAsk && hipMemGetInfo(&avail, &total) == hipSuccess && need > avail / 2)
+            e = hipErrorOutOfMemory;
         if (e == hipSuccess && !o.conv_ops[l][d].ensure(need)) e = hipErrorOutOfMemory;
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
@@ -1172,7 +1174,7 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
         const int chunk = std::max(8, 64 / groups);
         const double occ = (double)n / (double)nleaf;
         int nsplit = (int)std::ceil(occ / chunk);
-        while (nsplit < 8 && nleaf * nsplit < 65536) nsplit *= 2;
+        while (nsplit < 8 && nleaf * nsplit < 65536) nsplit = std::min(2 * nsplit, 8);
         nsplit = std::max(1, std::min(nsplit, (int)std::max<int64_t>(8, std::min<int64_t>(64, 16384 / nleaf))));
         while (nsplit > 1 && nleaf * nsplit >= ((int64_t)1 << 31)) nsplit /= 2;  // wavefront ids stay int
         HIPCHK(pl, launch_p2p<T>(nleaf, pl->levels, pl->xqp.ptr, pl->pstart.as<int32_t>(), pl->start.as<int32_t>(),

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kRedBlock) void k_finalize(
     // rounded to T: q' = q + d.  The energy is quadratic in the charges, so
     // 1/2 sum (2 q - q') phi' is that of q up to d^2, where 1/2 sum q phi' would miss
     // it by d (water's two charges are both 2e-8 low in FP32: 3M atoms, -2e-8).
-    auto weight = [](double exact, double held) { return 2.0 * exact - held; };
+    auto weight = [](double exact, double held) { return sizeof(T) == 8 ? exact : 2.0 * exact - held; };
     NSum e[1];
     for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n;
          s += (int64_t)gridDim.x * blockDim.x) {
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kRedBlock) void k_finalize(
         NSum t;
         t.merge(v[0].s, v[0].c);
         t.add(-M_PI * Q * Q / (2.0 * V * kappa * kappa));
-        t.add(0.5 * t00b * (sizeof(T) == 8 ? Q : weight(Q, m0[0])) * m0[0]);
+        t.add(0.5 * t00b * weight(Q, m0[0]) * m0[0]);
         t.add(2.0 * M_PI / (3.0 * V) * (Q * S - mu_w * mu2));
         host[8] = t.value();
         host[9] = v[0].value();
