@@ -1160,7 +1160,9 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
     const bool fork = !pl->in_batch;
     if (fork && !pl->side) return fail(pl, FMM_ERR_STATE, "plan has no side stream for the near field");
     hipStream_t ns = fork ? pl->side : s;
+    const bool late = conv_levels(pl) == 0;  // see below
     auto near_field = [&]() -> fmm_status {
+        if (fork && late) HIPCHK(pl, hipEventRecord(pl->ev_fork, s), "event record");
         if (fork) HIPCHK(pl, hipStreamWaitEvent(ns, pl->ev_fork, 0), "stream wait");
         const int64_t nleaf = level_cells(pl->levels);
         const int groups = plan_groups(pl, n);
@@ -1190,8 +1192,13 @@ static fmm_status run_fields(fmm_plan_t pl, int64_t n, const double *pos, const 
     // The near field is enqueued after the P2M: started before it, it takes every
     // wavefront slot of the chip and the P2M waits for most of its duration
     // (30,001 atoms: P2M 95 us instead of 21).  Both need the sorted atoms only,
-    // so its fork is recorded first.
-    if (fork) HIPCHK(pl, hipEventRecord(pl->ev_fork, s), "event record");
+    // so its fork is recorded first: the two start together.  Where every level
+    // takes the lists the far field is the longer by far and the P2M is not to
+    // share the chip at all: there the fork follows it (327,680 atoms, levels 5,
+    // p = 16, BF16: P2M 480 -> 86 us, whole call 16.5 -> 15.3 ms; with the
+    // convolution the near field would lose the P2M's time, 125,002 atoms 528 ->
+    // 560 us).
+    if (fork && !late) HIPCHK(pl, hipEventRecord(pl->ev_fork, s), "event record");
     if ((st = far_field<T>(pl, n, pl->xq.ptr, pl->phi_ff.as<double>(), pl->field_ff.as<T>(), near_field)) != FMM_OK)
         return st;
     if (fork) HIPCHK(pl, hipStreamWaitEvent(s, pl->ev_join, 0), "stream wait");

@@ -22,6 +22,8 @@ static struct Fake {
     int64_t widest = 0;  // wavefronts of the largest launch
     hipStream_t watched = nullptr;  // launches so far at the first wait of this stream
     long waited_at = -1;
+    std::map<hipEvent_t, long> recorded_at;  // launches so far at an event's last record
+    long first_wait_for = -1;                // that of the event first waited for
     long allocations_left = -1;  // -1: no limit
     bool capturing = false;
     dim3 grid, block;
@@ -83,14 +85,15 @@ hipError_t hipGetSymbolAddress(void **p, const void *) { *p = (void *)((uintptr_
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)std::malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) {
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    if (fk.first_wait_for < 0) fk.first_wait_for = fk.recorded_at[e];
     if (s == fk.watched && fk.waited_at < 0) fk.waited_at = fk.launched;
     return hipSuccess;
 }
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { fk.recorded_at[e] = fk.launched; return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { fk.capturing = true; return hipSuccess; }
@@ -364,6 +367,22 @@ static void batch_joins() {
     CHECK(hipStreamDestroy(s) == hipSuccess);
 }
 
+// The near field starts with the P2M beside a convolution, after it beside the lists:
+// five launches sort the atoms, the sixth is the P2M.
+static void near_field_fork() {
+    double *pos = device(3), *q = device(1), e;
+    for (int prec : {FMM_FP64, FMM_MIXED, FMM_MIXED_SPLIT16_M2L, FMM_MIXED_BF16_M2L}) {
+        fmm_plan_t plan = nullptr;
+        CHECK(fmm_plan(20.0, 4, 4, &plan) == FMM_OK);
+        CHECK(fmm_plan_config(plan, prec, 0.0, nullptr) == FMM_OK);
+        const long before = fk.launched;
+        fk.first_wait_for = -1;
+        CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+        CHECK(fk.first_wait_for - before == (conv_levels(plan) > 0 ? 5 : 6));
+        fmm_destroy(plan);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
@@ -373,6 +392,7 @@ int main(int argc, char **argv) {
     else if (c == "options_without_memory") options_without_memory();
     else if (c == "crowded_leaves") crowded_leaves();
     else if (c == "batch_joins") batch_joins();
+    else if (c == "near_field_fork") near_field_fork();
     else if (c == "old_cache_line" && argc > 2) old_cache_line(argv[2]);
     else {
         std::printf("no such case\n");

@@ -62,3 +62,7 @@ def test_cache_lines_of_other_kernels_are_not_taken(check, tmp_path):
 
 def test_batch_waits_for_its_boxes_after_the_last(check):
     assert check("batch_joins") == (0, "ok")
+
+
+def test_near_field_forks_where_the_far_field_needs_it(check):
+    assert check("near_field_fork") == (0, "ok")
