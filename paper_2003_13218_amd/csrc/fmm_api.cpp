@@ -516,8 +516,7 @@ static fmm_status ensure_conv_ops(fmm_plan_t pl) {
     return FMM_OK;
 }
 
-static fmm_status ensure_m2l_ops(fmm_plan_t pl, bool want64 = false) {
-    if (m2l_ops_ready(pl, want64)) return FMM_OK;
+static fmm_status try_m2l_ops(fmm_plan_t pl, bool want64) {
     fmm_status st = ensure_conv_ops(pl);
     if (st != FMM_OK) return st;
     if (m2l_ops_ready(pl, want64)) return FMM_OK;
@@ -598,6 +597,14 @@ static fmm_status ensure_m2l_ops(fmm_plan_t pl, bool want64 = false) {
         HIPCHK(pl, hipMemcpy(pl->op->ops32.ptr, sw.data(), ne * sizeof(float), hipMemcpyHostToDevice), "M2L upload");
     }
     return FMM_OK;
+}
+
+// List operators that find no memory take that of the convolution's blocks too
+static fmm_status ensure_m2l_ops(fmm_plan_t pl, bool want64 = false) {
+    if (m2l_ops_ready(pl, want64)) return FMM_OK;
+    fmm_status st = try_m2l_ops(pl, want64);
+    while (st == FMM_ERR_NOMEM && conv_give_back(pl)) st = try_m2l_ops(pl, want64);
+    return st;
 }
 
 static fmm_status ensure_side_streams(fmm_plan_t pl);
@@ -1982,6 +1989,22 @@ static fmm_status batch_graph(fmm_plan_t pl, fmm_plan::Graph &g, const std::vect
     return FMM_OK;
 }
 
+// The operators of all boxes that hold atoms; they share one set, so that what one
+// box gives back for its lists another may have counted on: a second pass, by when
+// all are on the lists
+static fmm_status batch_m2l_ops(fmm_plan_t pl, const int64_t *off, bool want64) {
+    for (int pass = 0; pass < 2; ++pass)
+        for (size_t w = 0; w < pl->sub.size(); ++w) {
+            if (off[w + 1] == off[w]) continue;
+            const fmm_status st = ensure_m2l_ops(pl->sub[w], want64);
+            if (st != FMM_OK) {
+                pl->err = "box " + std::to_string(w) + ": " + pl->sub[w]->err;
+                return st;
+            }
+        }
+    return FMM_OK;
+}
+
 extern "C" fmm_status fmm_energy_forces_batch(fmm_plan_t pl, const int64_t *offsets, const double *pos,
                                               const double *q, double *energies, double *forces) {
     if (!pl) return fail(nullptr, FMM_ERR_INVALID, "plan is NULL");
@@ -2003,11 +2026,7 @@ extern "C" fmm_status fmm_energy_forces_batch(fmm_plan_t pl, const int64_t *offs
         }
     }
     // after every workspace, which may take the operators' memory
-    for (size_t w = 0; w < nb; ++w)
-        if (offsets[w + 1] > offsets[w] && (st = ensure_m2l_ops(pl->sub[w])) != FMM_OK) {
-            pl->err = "box " + std::to_string(w) + ": " + pl->sub[w]->err;
-            return st;
-        }
+    if ((st = batch_m2l_ops(pl, offsets, false)) != FMM_OK) return st;
     if ((st = batch_inputs(pl)) != FMM_OK) return st;
     st = batch_branches(pl, offsets, [&](size_t w) -> fmm_status {
         fmm_plan_t b = pl->sub[w];
@@ -2049,14 +2068,8 @@ static fmm_status solute_solvent_batch(fmm_plan_t pl, const uint8_t *mask, const
     const int64_t *off = pl->batch_off.data();
     if (off[nb] > off[0] && !mask) return fail(pl, FMM_ERR_INVALID, "mask is NULL");
     HIPCHK(pl, hipSetDevice(pl->device), "hipSetDevice");
-    for (size_t w = 0; w < nb; ++w) {
-        if (off[w + 1] == off[w]) continue;
-        const fmm_status so = ensure_m2l_ops(pl->sub[w], (pl->uv_scheme & FMM_UV_SPARSE) != 0);
-        if (so != FMM_OK) {
-            pl->err = "box " + std::to_string(w) + ": " + pl->sub[w]->err;
-            return so;
-        }
-    }
+    const fmm_status so = batch_m2l_ops(pl, off, (pl->uv_scheme & FMM_UV_SPARSE) != 0);
+    if (so != FMM_OK) return so;
     std::vector<int64_t> key(pl->batch_off);
     key.push_back((int64_t)(uintptr_t)mask);
     key.push_back(pl->prec);

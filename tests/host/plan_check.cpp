@@ -216,6 +216,7 @@ static void call_after_no_memory() {
         (void)fmm_solute_solvent_energy(plan, (const uint8_t *)q, &u);
         fk.allocations_left = -1;
         CHECK(fmm_solute_solvent_energy(plan, (const uint8_t *)q, &u) == FMM_OK);
+        CHECK(fmm_plan_config(plan, FMM_FP64, 0.0, nullptr) == FMM_OK);  // what was given back for them
         if (k == 12) want = fk.live.size();
         if (fk.live.size() != want) {
             std::printf("%d allocations first: %zu buffers, not %zu\n", k, fk.live.size(), want);
@@ -383,6 +384,40 @@ static void near_field_fork() {
     }
 }
 
+// And so does that of list operators that need it, in a batch for all boxes.
+static void lists_short_of_memory() {
+    double *pos = device(3), *q = device(1), e, u;
+    void *others = nullptr;
+    fmm_plan_t plan = nullptr;
+    CHECK(fmm_plan(100.0, 6, 12, &plan) == FMM_OK);
+    CHECK(fmm_plan_config(plan, FMM_MIXED, 0.0, nullptr) == FMM_OK);
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    CHECK(fmm_solute_solvent_energy(plan, (const uint8_t *)q, &u) == FMM_OK);
+    CHECK(conv_levels(plan) == 6);
+    CHECK(hipMalloc(&others, fk.total - fk.used - ((size_t)100 << 20)) == hipSuccess);
+    CHECK(fmm_plan_options(plan, FMM_BOUNDARY_CONDUCTING, FMM_UV_SPARSE) == FMM_OK);  // 470 MiB
+    CHECK(conv_levels(plan) == 0);
+    CHECK(fmm_energy_forces(plan, 1000, pos, q, &e, nullptr, nullptr) == FMM_OK);
+    CHECK(fmm_solute_solvent_energy(plan, (const uint8_t *)q, &u) == FMM_OK);
+    fmm_destroy(plan);
+    CHECK(hipFree(others) == hipSuccess);
+
+    const double box[3] = {100.0, 100.0, 100.0};
+    const int levels[3] = {6, 5, 7};
+    const int64_t off[4] = {0, 1000, 2000, 3000};
+    double energies[3], uv[3];
+    CHECK(fmm_plan_batch(3, box, nullptr, levels, 12, &plan) == FMM_OK);
+    CHECK(fmm_plan_config(plan, FMM_MIXED, 0.0, nullptr) == FMM_OK);
+    CHECK(fmm_energy_forces_batch(plan, off, pos, q, energies, nullptr) == FMM_OK);
+    CHECK(fmm_solute_solvent_energy_batch(plan, (const uint8_t *)q, uv) == FMM_OK);
+    CHECK(hipMalloc(&others, fk.total - fk.used - ((size_t)100 << 20)) == hipSuccess);
+    CHECK(fmm_plan_options(plan, FMM_BOUNDARY_CONDUCTING, FMM_UV_SPARSE) == FMM_OK);
+    CHECK(fmm_energy_forces_batch(plan, off, pos, q, energies, nullptr) == FMM_OK);
+    CHECK(fmm_solute_solvent_energy_batch(plan, (const uint8_t *)q, uv) == FMM_OK);
+    fmm_destroy(plan);
+    CHECK(hipFree(others) == hipSuccess);
+}
+
 int main(int argc, char **argv) {
     const std::string c = argc > 1 ? argv[1] : "";
     if (c == "batch_replay") batch_replay();
@@ -390,6 +425,7 @@ int main(int argc, char **argv) {
     else if (c == "call_after_no_memory") call_after_no_memory();
     else if (c == "short_of_memory") short_of_memory();
     else if (c == "options_without_memory") options_without_memory();
+    else if (c == "lists_short_of_memory") lists_short_of_memory();
     else if (c == "crowded_leaves") crowded_leaves();
     else if (c == "batch_joins") batch_joins();
     else if (c == "near_field_fork") near_field_fork();

@@ -48,6 +48,10 @@ def test_workspaces_take_the_memory_of_operators(check):
     assert check("short_of_memory") == (0, "ok")
 
 
+def test_list_operators_take_the_memory_of_operators(check):
+    assert check("lists_short_of_memory") == (0, "ok")
+
+
 def test_options_report_operators_that_do_not_fit(check):
     assert check("options_without_memory") == (0, "ok")
 
