@@ -198,7 +198,7 @@ def roofline_lists(w, p, st, prec_name, info):
                              "executed_with_padding": executed},
             "frac_dense_equivalent": round(tflops(dense) / peak, 4),
             "frac_executed_with_padding": round(tflops(executed) / peak, 4),
-            "folding": "profiles/m2l_folding.md"}
+            "folding": ("none", "pairs (t, -t)", "orbits of the two-axis flips")[info["m2l_scheme"]]}
 
 
 # FP32 and FP64 peaks of the vector units (TFLOP/s)

@@ -103,12 +103,13 @@ typedef enum {
  * Precomputes in FP64 the scale-invariant M2M / M2L / L2L operators and the
  * lattice tensor of eq. 12.  The M2L of levels 1 .. 6 runs as a convolution
  * over the level's periodic grid with operators per wave number on the device:
- * about 0.42 8^levels K^2 elements of the level's type (27 Kp^2 per triple of
- * wave numbers; 1,000,000 atoms, levels 5, p 12: 1.4 GB in FP32, 2.7 GB in
- * FP64).  A level whose operators would take more than 64 GiB, a quarter of
- * the device's memory or (past 64 MiB) half of what is free takes the
- * interaction lists, and a workspace that finds no memory takes the operators', whose levels then take
- * the lists until the next fmm_plan_config or fmm_plan_tuning.  The
+ * 27 Kp^2 elements of the level's type per triple of wave numbers (kx >= ky,
+ * kz; 1, 6, 18, 75, 405 and 2,601 triples at levels 1 .. 6; 1,000,000 atoms,
+ * levels 5, p 12: 1.4 GB for level 5 in FP32, 2.7 GB in FP64).  A level whose
+ * operators would take more than 64 GiB, a quarter of the device's memory or
+ * (past 64 MiB) half of what is free takes the interaction lists.  A workspace
+ * or list operators that find no memory take the convolution's, whose levels
+ * then take the lists until the next fmm_plan_config or fmm_plan_tuning.  The
  * operators of FMM_FP64 are built here, unless they are more than 1 GiB and the
  * plan is past the scratch of fmm_energy_forces_noalloc: then fmm_plan_config
  * or the first evaluation builds what the plan's mode needs.
@@ -133,9 +134,10 @@ fmm_status fmm_plan_config(fmm_plan_t plan, int precision, double kappa, void *h
  *                shallow levels the cells are large and their M2L terms
  *                cancel strongly, so FP32 there costs accuracy: on the
  *                1,000,000-atom water box (levels 5, p 12) the default
- *                gives an RMS potential error of 1.8e-6 against the FP64
- *                Ewald sum, 4 gives 7e-7 at about 0.8 ms more per
- *                evaluation.  Ignored in FMM_FP64 (everything is FP64).
+ *                gives an RMS potential error of 4.0e-7 against the FP64
+ *                Ewald sum, 4 gives 3.2e-7 at about 0.1 ms more per
+ *                evaluation (with the interaction lists 1.8e-6 and 7e-7, at
+ *                0.8 ms more).  Ignored in FMM_FP64 (everything is FP64).
  *                -1 keeps the current value.
  *   p2p_groups   source groups of the near-field kernel (1, 2, 4, 8, 16: the
  *                atoms of a leaf are split in target chunks of at most 64 /

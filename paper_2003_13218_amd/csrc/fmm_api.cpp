@@ -371,7 +371,7 @@ static int upper_m2l_levels(fmm_plan_t pl) {
 // Levels 1 .. conv_levels(pl) take the M2L as a convolution (k_conv.hip), the
 // finer ones the interaction lists.  The convolution does a level in about the
 // time its blocks take to stream (finest level of the 1M-atom box, p = 12: lists
-// 5.9 ms, convolution 0.7 ms in FP32; 13.4 and 1.1 ms in FP64), so it is taken
+// 5.9 ms, convolution 0.55 ms in FP32; 13.4 and 0.86 ms in FP64), so it is taken
 // wherever the blocks (their bytes grow with 8^level K^2) fit: levels up
 // to 6 (lines of 64 cells in registers), at most a quarter of the device's
 // memory and 64 GiB for a level (p = 20 at level 6 in FP64: 113 GB), and at most
@@ -1820,7 +1820,9 @@ extern "C" void fmm_destroy(fmm_plan_t pl) {
 // Cost model for the tree depth of one box (seconds, MI355X): P2P pairs
 // N * 125 N / 8^L, M2L flops 2 Kp^2 * 875 per cell summed over levels 1..L,
 // a fixed per-level launch cost, and the per-atom expansion work.  The rates
-// were measured with the kernels of this library on the 1M-atom box; the
+// were measured on the 1M-atom box with the interaction lists and one target a
+// lane, so the depths chosen are those of that far field: shallower than what the
+// convolution would take (32 windows: depth 3 here, 3 or 4 when timed).  The
 // autotuner (fmm_autotune_batch) replaces the model's choice by timings.
 static double depth_cost(int64_t n, int levels, int p, int prec) {
     const double Kp = padded_coeffs(p);

@@ -22,7 +22,7 @@
 // reciprocal square root (FP32: 2.9 and 8.6 cycles of a SIMD at 2.4 GHz with all
 // operands in vector registers), 3.8e9 pairs in 4.7e9 lane slots on the 1M-atom
 // box: 1.5 ms at that rate, 2.03 ms measured with the loop, the leaf changes and
-// the return path of the source loads beside them.
+// the return path of the source loads (90% busy) beside them.
 #include <type_traits>
 
 #include "fmm_internal.h"
