@@ -268,7 +268,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(p2p_waves<T
 // call 707 -> 571 us; 30,001 atoms 383 -> 339 us; with 16: 622 and 361 us).  Above,
 // the near field or the memory-bound convolution is the longer, and 4 keep the
 // slots fuller (1M atoms, levels 5: 2.88 ms against 3.03; 3M, levels 6: 5.96
-// against 6.37).  The split into wavefronts and with it every sum is the same.
+// against 6.37).  By the level alone, over 1 to 244 atoms a leaf and both types: at
+// levels 3 and 4 8 are 2 to 41% faster (but 1% and 2.5% slower at 6 and 195 atoms a
+// leaf of level 3), at levels 5 and 6 3 to 8% slower.  The split into wavefronts and
+// with it every sum is the same.
 static int p2p_block_waves(int levels) { return levels <= 4 ? 8 : 4; }
 
 // nsrc_max bounds the padded source count (buffer loads need every leaf's
